@@ -168,32 +168,6 @@ __device__ __forceinline__ void x_piece_offsets(int f, int& o1, int& o2) {  // i
     o2 = f < 12 ? 48 + 4 * f : o1 + 4;
   }
 }
-template <int BITS>
-__device__ __forceinline__ u32x4 x_piece(u32x2 lo, u32x2 hi) {
-  u32x4 o;
-  if (BITS == 4) {  // [x0 x1][x2 x3] [x4 x5][x6 x7] -> [x0 x4][x1 x5][x2 x6][x3 x7]
-    o.x = perm(hi.x, lo.x, 0x05040100u);
-    o.y = perm(hi.x, lo.x, 0x07060302u);
-    o.z = perm(hi.y, lo.y, 0x05040100u);
-    o.w = perm(hi.y, lo.y, 0x07060302u);
-  } else {  // per four: [x0 x1][x2 x3] -> [x0 x2][x1 x3]
-    o.x = perm(lo.y, lo.x, 0x05040100u);
-    o.y = perm(lo.y, lo.x, 0x07060302u);
-    o.z = perm(hi.y, hi.x, 0x05040100u);
-    o.w = perm(hi.y, hi.x, 0x07060302u);
-  }
-  return o;
-}
-
-// Four int8 activation codes (the bytes of b) as exact binary16 pairs (v0, v1), (v2, v3):
-// v + 128 in the fraction bits of 1024, minus 1152.
-__device__ __forceinline__ u32x2 i8x4_to_h4(uint32_t b) {
-  const uint32_t u = b ^ 0x80808080u;
-  const uint32_t m1152 = 0xE480E480u;  // (-1152, -1152)
-  return u32x2{hadd2(perm(0u, u, 0x0C010C00u) | kMagic1024, m1152),
-               hadd2(perm(0u, u, 0x0C030C02u) | kMagic1024, m1152)};
-}
-
 // A8: X holds int8 activation codes [m][k] (qx_quantize_a8) and sx their per-row
 // scales; the codes enter the products as exact binary16 integers and each output
 // row is multiplied by its scale before rounding. Otherwise X is fp16 [m][k].

@@ -1,0 +1,669 @@
+// Quantized GEMM for many activation rows: Y[m][n] = sum_k X[m][k] W'[n][k] on the fp16
+// matrix cores with wave tiles of 16*MT activation rows x 16*NT weight rows.
+//
+// What bounds it. A 16x16x32 product takes 16 cycles of a SIMD and the LDS of a compute
+// unit delivers 128 bytes a cycle to its four SIMDs, so a wave tile of 128 x 32 already
+// reads activation fragments as fast as LDS can deliver them; at 128 x 64 these reads take
+// half of that. Weights never pass through LDS as fp16: every wave decodes its own weight
+// rows from packed codes in registers, and each decoded fragment feeds MT products. Timed
+// with parts left out (22016x4096 uniform-4 g128, m = 2048, 483 us with 16-byte code runs):
+// the products, their activation reads and the barriers alone take 260 us, decoding adds 30,
+// LDS writes 40, the loads of activations 70 and those of codes 90; hence code runs of SC
+// chunks (below), which took that product to 401 us.
+//
+// Block. WM x 4 waves: 4 take different weight rows, WM different activation rows. A round
+// is half a chunk (64 k): its activations sit in one of two LDS buffers in decoder pair
+// order, the codes of SC chunks (a super-round) in one of two code buffers as
+// [slice][row][chunk] pieces of 16 bytes. The next round's activations and the next
+// super-round's codes travel from memory into registers meanwhile and are written to LDS
+// after their round: one barrier a round. Blocks of 4 waves and 128 x 256 or less use at
+// most half of the LDS and of the registers in most formats, so two or three of them share
+// a compute unit and one decodes while another multiplies; a block of 256 x 256 has two
+// waves on every SIMD itself.
+//
+// LDS banks. Activation rows of 128 bytes with 16-byte pieces swizzled by row (padding by
+// 16 bytes left 37 % of the LDS cycles to conflicts, because the lanes that the LDS serves
+// together come from two pieces), codes swizzled so that 16 rows of one chunk hit all banks.
+//
+// k order. k-step T of a chunk (32 of 128 k) takes 8 consecutive codes 8f .. 8f + 7 in lane
+// group g (f = 4T + g), so that a k-step lies in one quantization group:
+//   b = 4: code dword f;
+//   b = 3: T = 0: bits 0-2 of dwords 2g, 2g+1; T = 1: bits 0-2 of dwords 8+2g, 9+2g (g < 2)
+//          or bits 3-5 of dwords 2(g-2), 2(g-2)+1; T = 2: bits 3-5 of dwords 4+2g, 5+2g;
+//          T = 3: the spare codes of dwords 2g, 2g+1.
+//
+// A8: X holds int8 codes (qx_quantize_a8), which enter the products as exact binary16
+// integers; Y is scaled by the row's sx. Uniform and Q4X weights then enter as the exact
+// integers q - z or the sub-codebook's entries, and the sum of a group (of half a group of
+// 128) is scaled by its s in fp32: at most 64 * 15 * 127 for uniform codes, exact in fp32.
+#include <type_traits>
+
+#include "qx_device.h"
+#include "qx_internal.h"
+
+namespace qx {
+namespace {
+
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int kXRow = 128;  // LDS bytes of one activation row of a round: 64 fp16
+
+template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC>
+struct TileShape {
+  static constexpr int kThreads = 256 * WM;
+  static constexpr int BM = 16 * MT * WM, BN = 64 * NT, NG = 128 / G;
+  static constexpr int kTable = 2 << BITS;  // bytes of a codebook group's table
+  // LDS planes of BN rows x kMUnit bytes that hold a chunk's groups as the decoders take them
+  // (prepared once a block when they are stored): uniform (s, s) and -(1024 + z), the lookup
+  // tables of 8 entries, or the Q4X scales and selectors
+  static constexpr int kMUnit = KIND == QX_CODEBOOK ? 16 : 8;
+  static constexpr int kMPlanes = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 1 : NG * kTable / 16;  // per chunk
+  static constexpr int kXBuf = BM * kXRow, kCBuf = BITS * BN * SC * 16, kMBuf = kMPlanes * SC * BN * kMUnit;
+  static constexpr int kLds = 2 * (kXBuf + kCBuf + kMBuf) + (KIND == QX_Q4X ? 128 : 0);
+  // waves on a SIMD for which registers are allocated
+  static constexpr int kWaves = WM == 2 || 2 * kLds <= kLdsBytes ? 2 : 1;
+};
+
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+__device__ __forceinline__ BufferRsrc buffer(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
+}
+
+// What decodes a fragment: the lane's code dwords (b = 4: L.x; b = 3: L, and H for the
+// spare codes) and its group's constants or table.
+template <int BITS, int KIND>
+struct RawFrag {
+  u32x2 L, H;
+  uint32_t sp, z0;  // uniform: (s, s) and -(1024 + z) pairs; Q4X: sp
+  LutGroup<BITS> lut;
+};
+
+template <int BITS, int KIND, bool SCALE>
+__device__ __forceinline__ uint32_t level(uint32_t mq, uint32_t zc, uint32_t sp) {
+  const uint32_t v = hadd2(mq, zc);
+  return SCALE ? hmul2(v, sp) : v;
+}
+
+// B fragment of k-step T.
+template <int BITS, int KIND, int T, bool SCALE>
+__device__ __forceinline__ h8_t tile_frag(const RawFrag<BITS, KIND>& gd, const DecodeConsts& k, uint32_t t1,
+                                          uint32_t up, uint32_t dn, uint32_t ssh) {
+  // -(M + z) for M = 128 (b = 3) or 64 (b = 4), and 16: z in steps of 8 or 16, and 64
+  const uint32_t z1 = BITS == 3 ? (gd.z0 << 3) + (0xD800D800u - (0xE400E400u << 3))
+                                : (gd.z0 << 4) + (0xD400D400u - (0xE400E400u << 4));
+  const uint32_t z2 = (gd.z0 << 6) + (0xCC00CC00u - (0xE400E400u << 6));
+  if constexpr (BITS == 4) {
+    const uint32_t D = gd.L.x;
+    if constexpr (KIND == QX_UNIFORM) {
+      const uint32_t Ds = D >> 8;
+      return frag(level<4, KIND, SCALE>((D & k.m000f) | k.mag1024, gd.z0, gd.sp),    // (0, 4)
+                  level<4, KIND, SCALE>((D & k.m00f0) | k.mag64, z1, gd.sp),      // (1, 5)
+                  level<4, KIND, SCALE>((Ds & k.m000f) | k.mag1024, gd.z0, gd.sp),   // (2, 6)
+                  level<4, KIND, SCALE>((Ds & k.m00f0) | k.mag64, z1, gd.sp));    // (3, 7)
+    } else {
+      uint32_t elo, ehi, olo, ohi;
+      lut4_bytes(gd.lut, D & 0x0F0F0F0Fu, elo, ehi);         // codes 0 2 4 6
+      lut4_bytes(gd.lut, (D >> 4) & 0x0F0F0F0Fu, olo, ohi);  // codes 1 3 5 7
+      const uint32_t p0 = perm(ehi, elo, 0x06020400u), p1 = perm(ohi, olo, 0x06020400u);
+      const uint32_t p2 = perm(ehi, elo, 0x07030501u), p3 = perm(ohi, olo, 0x07030501u);
+      if constexpr (KIND == QX_Q4X && SCALE)  // fp16(s * CB[t][q]): one rounding, as qx_dequant
+        return frag(hmul2(p0, gd.sp), hmul2(p1, gd.sp), hmul2(p2, gd.sp), hmul2(p3, gd.sp));
+      return frag(p0, p1, p2, p3);
+    }
+  } else {
+    const uint32_t d[2] = {gd.L.x, gd.L.y}, h[2] = {gd.H.x, gd.H.y};
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t D = T == 1 ? d[i] >> t1 : d[i];  // T = 1: both field kinds to bits 0-2
+      if constexpr (KIND == QX_UNIFORM) {
+        const uint32_t Ds = D >> 8;
+        if constexpr (T < 2) {
+          w[2 * i] = level<3, KIND, SCALE>((D & k.m0007) | k.mag1024, gd.z0, gd.sp);
+          w[2 * i + 1] = level<3, KIND, SCALE>((Ds & k.m0007) | k.mag1024, gd.z0, gd.sp);
+        } else if constexpr (T == 2) {
+          w[2 * i] = level<3, KIND, SCALE>((D & k.m0038) | k.mag128, z1, gd.sp);
+          w[2 * i + 1] = level<3, KIND, SCALE>((Ds & k.m0038) | k.mag128, z1, gd.sp);
+        } else {
+          const uint32_t u0 = ((h[i] << up) & k.m0100) | k.mag16, u1 = ((h[i] >> dn) & k.m0100) | k.mag16;
+          w[2 * i] = level<3, KIND, SCALE>((D & k.m00c0) | u0, z2, gd.sp);
+          w[2 * i + 1] = level<3, KIND, SCALE>((Ds & k.m00c0) | u1, z2, gd.sp);
+        }
+      } else {
+        const uint32_t S = T < 2    ? D & 0x07070707u
+                           : T == 2 ? (D >> 3) & 0x07070707u
+                                    : ((D >> 6) & 0x03030303u) | ((h[i] >> ssh) & 0x04040404u);
+        lut3_pairs(gd.lut, S, w[2 * i], w[2 * i + 1]);
+      }
+    }
+    return frag(w[0], w[1], w[2], w[3]);
+  }
+}
+
+template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, bool A8,
+          int WAVES = TileShape<BITS, KIND, G, MT, NT, WM, SC>::kWaves>
+__global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
+    const char* __restrict__ packed, const void* __restrict__ Xv, const float* __restrict__ sx,
+    uint16_t* __restrict__ Y, int n, int k, int m, int nx, int my, int vec) {
+  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC>;
+  constexpr int NTH = TS::kThreads, BM = TS::BM, BN = TS::BN, NG = TS::NG;
+  constexpr bool kSums = A8 && KIND != QX_CODEBOOK;  // group sums scaled in fp32
+  constexpr int XP = BM * 8 / NTH;                   // 16-byte activation pieces per thread and round
+  constexpr int CT = BITS * BN * SC, CP = (CT + NTH - 1) / NTH;
+  constexpr int MTOT = (KIND == QX_CODEBOOK ? TS::kMPlanes : 1) * BN * SC;  // table pieces, or rows x chunks
+  constexpr int MP = (MTOT + NTH - 1) / NTH;
+  constexpr int MD = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 2 : 4;  // dwords of one
+  static_assert(BM * 8 % NTH == 0, "activation pieces divide evenly");
+  __shared__ __align__(16) char lds[TS::kLds];
+  char* const xs = lds;
+  char* const cts = lds + 2 * TS::kXBuf;
+  char* const mts = cts + 2 * TS::kCBuf;
+  uint32_t* const q4lut = reinterpret_cast<uint32_t*>(mts + 2 * TS::kMBuf);
+
+  // Block -> (weight tile bn, activation tile bm). Workgroups are dealt to the 8 XCDs
+  // round-robin; an XCD takes every eighth weight tile and walks them with up to 8
+  // activation tiles together, so that the tiles in flight in its L2 form a square.
+  const int nb = (nx + 7) >> 3, q = blockIdx.x >> 3;
+  const int hi = q / (nb * 8), gsz = min(8, my - hi * 8), rem = q - hi * nb * 8;
+  const int bm = hi * 8 + rem % gsz, bn = (rem / gsz) * 8 + (blockIdx.x & 7);
+  if (bn >= nx) return;  // padding blocks: whole block, before any barrier
+  const int n0 = bn * BN, m0 = bm * BM;
+  const int C = k >> 7, G_row = k / G;
+  const size_t meta_off = (size_t)n * k * BITS / 8;
+  const int t = threadIdx.x, lane = t & 63, g = lane >> 4, li = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wn = wave & 3, wm = wave >> 2;
+  const DecodeConsts kc = decode_consts();
+  const uint32_t t1 = g < 2 ? 0u : 3u, up = g < 2 ? 2u : 1u, dn = g < 2 ? 6u : 7u, ssh = g < 2 ? 4u : 5u;
+
+  // Loads of the next round or chunk into registers (rows and chunks clamped in bounds;
+  // the clamped copies are never stored to Y or never multiplied) and their LDS writes.
+  u32x4 xr[XP], cr[CP];
+  uint32_t mr[MP][MD];
+  // Buffer loads: one 32-bit offset a thread and piece, the chunk in a scalar register, rows
+  // past the matrix outside the bounds (they read 0). The 64-bit addresses that the compiler
+  // keeps for plain loads would not leave room for the accumulators.
+  constexpr int kXB = A8 ? 1 : 2;  // bytes of an activation
+  constexpr int kMRow = KIND == QX_UNIFORM ? 4 : KIND == QX_Q4X ? 2 : TS::kTable;  // bytes of a group's word, scale or table
+  const int xrows = min(BM, m - m0), wrows = min(BN, n - n0);
+  const BufferRsrc xres = buffer(static_cast<const char*>(Xv) + (size_t)m0 * k * kXB, xrows * k * kXB);
+  const BufferRsrc cres = buffer(packed + (size_t)n0 * BITS * C * 16, wrows * BITS * C * 16);
+  const BufferRsrc mres = buffer(packed + meta_off + (size_t)n0 * G_row * kMRow, wrows * G_row * kMRow);
+  const int sel_words = (G_row + 15) / 16;
+  const BufferRsrc sres = buffer(packed + meta_off + meta_off / 16 + (size_t)n0 * sel_words * 4,
+                                 KIND == QX_Q4X ? wrows * sel_words * 4 : 0);
+  const int xoff = (t >> 3) * k * kXB + (t & 7) * 8 * kXB;
+  auto load_x = [&](int c, int h) {
+    const int so = (min(c, C - 1) * 128 + h * 64) * kXB;
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      const int so_i = so + i * (NTH / 8) * k * kXB;  // uniform
+      if constexpr (A8) {
+        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(xres, xoff, so_i, 0));
+        xr[i].x = v.x; xr[i].y = v.y;
+      } else {
+        xr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, xoff, so_i, 0));
+      }
+    }
+  };
+  auto store_x = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < XP; ++i) {
+      const int p = t + i * NTH;
+      u32x2 lo = {xr[i].x, xr[i].y}, hh = {xr[i].z, xr[i].w};
+      if constexpr (A8) {
+        hh = i8x4_to_h4(xr[i].y);
+        lo = i8x4_to_h4(xr[i].x);
+      }
+      *reinterpret_cast<u32x4*>(xs + buf * TS::kXBuf + (p >> 3) * kXRow + ((p ^ (p >> 4)) & 7) * 16) = x_piece<BITS>(lo, hh);
+    }
+  };
+  // Code piece p = t + i * NTH of a super-round (SC chunks): SC neighbouring lanes take a
+  // row's SC pieces of a slice, in an order that spreads 16 rows over the LDS banks.
+  int coff[CP], moff[MP];
+#pragma unroll
+  for (int i = 0; i < CP; ++i) {
+    const int p = t + i * NTH, q = p / SC;
+    const int row = q % BN, cc = (p % SC) ^ (SC == 2 ? (row >> 3) & 1 : 0);
+    if constexpr (BN * SC % NTH == 0)  // the slice is uniform and goes to the scalar offset
+      coff[i] = (row * BITS * C + cc) * 16;
+    else
+      coff[i] = ((row * BITS + min(q / BN, BITS - 1)) * C + cc) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < MP; ++i) {
+    const int p = min(t + i * NTH, MTOT - 1);
+    if constexpr (KIND == QX_CODEBOOK)  // a row's tables of the super-round are one run
+      moff[i] = p / (TS::kMPlanes * SC) * G_row * kMRow + p % (TS::kMPlanes * SC) * 16;
+    else if constexpr (KIND == QX_UNIFORM)
+      moff[i] = (p / SC * G_row + p % SC * NG) * 4;
+    else
+      moff[i] = p;
+  }
+  // Codes and tables of super-round j. Past the last chunk of a row the loads run on into
+  // what follows (or out of bounds, 0); it is never multiplied.
+  const int last_j = (C - 1) / SC;
+  auto load_codes = [&](int j) {
+    const int c = min(j, last_j) * SC;
+#pragma unroll
+    for (int i = 0; i < CP; ++i)
+      cr[i] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                     cres, coff[i], (BN * SC % NTH == 0 ? (i * NTH / (BN * SC)) * C + c : c) * 16, 0));
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      if constexpr (KIND == QX_CODEBOOK) {
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(mres, moff[i], c * NG * kMRow, 0));
+        mr[i][0] = v.x; mr[i][1] = v.y; mr[i][2] = v.z; mr[i][3] = v.w;
+      } else if constexpr (KIND == QX_UNIFORM) {
+        const int so = c * NG * 4;
+        if constexpr (NG == 1) {
+          mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, moff[i], so, 0);
+        } else if constexpr (NG == 2) {
+          const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(mres, moff[i], so, 0));
+          mr[i][0] = v.x; mr[i][1] = v.y;
+        } else {
+          const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(mres, moff[i], so, 0));
+          mr[i][0] = v.x; mr[i][1] = v.y; mr[i][2] = v.z; mr[i][3] = v.w;
+        }
+      } else {  // the scales of a chunk's groups and their selectors (4 bits)
+        const int row = moff[i] / SC, cm = c + moff[i] % SC;
+        mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, row * G_row * 2 + moff[i] % SC * 4, 4 * c, 0);
+        mr[i][1] = __builtin_amdgcn_raw_buffer_load_b32(sres, (row * sel_words + cm / 8) * 4, 0, 0) >> (4 * (cm % 8));
+      }
+    }
+  };
+  auto store_codes = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < CP; ++i) {
+      const int p = t + i * NTH;
+      if (CT % NTH == 0 || p < CT) *reinterpret_cast<u32x4*>(cts + buf * TS::kCBuf + p * 16) = cr[i];
+    }
+    char* const mb = mts + buf * TS::kMBuf;
+#pragma unroll
+    for (int i = 0; i < MP; ++i) {
+      const int p = t + i * NTH;
+      if (MTOT % NTH == 0 || p < MTOT) {
+        if constexpr (KIND == QX_CODEBOOK) {
+          *reinterpret_cast<u32x4*>(mb + (p % (TS::kMPlanes * SC) * BN + p / (TS::kMPlanes * SC)) * 16) =
+              u32x4{perm(mr[i][1], mr[i][0], 0x06040200u), perm(mr[i][3], mr[i][2], 0x06040200u),
+                    perm(mr[i][1], mr[i][0], 0x07050301u), perm(mr[i][3], mr[i][2], 0x07050301u)};
+        } else if constexpr (KIND == QX_Q4X) {
+          *reinterpret_cast<u32x2*>(mb + (p % SC * BN + p / SC) * 8) = u32x2{mr[i][0], mr[i][1]};
+        } else {
+#pragma unroll
+          for (int j = 0; j < NG; ++j) {
+            const uint32_t w = mr[i][j];
+            // z is an integer-valued fp16: the bits of -(1024 + z) are those of -1024 plus z
+            const uint32_t z = (uint32_t)(unsigned short)__builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
+            *reinterpret_cast<u32x2*>(mb + ((p % SC * NG + j) * BN + p / SC) * 8) =
+                u32x2{perm(w, w, 0x01000100u), (0xE400u + z) * 0x00010001u};
+          }
+        }
+      }
+    }
+  };
+
+  f4_t acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4_t{0.f, 0.f, 0.f, 0.f};
+
+  // Codes and group constants of the fragment of weight rows 16 nt .. of this wave at k-step
+  // T of chunk cc of the super-round in code buffer cb.
+  auto read_raw = [&](auto tc, int cb, int cc, int nt) {
+    constexpr int T = decltype(tc)::value;
+    RawFrag<BITS, KIND> r;
+    const int row = wn * 16 * NT + 16 * nt + li;
+    constexpr int SL = BN * SC * 16;  // bytes of a slice
+    const char* const cr0 = cts + cb * TS::kCBuf + row * SC * 16 + (SC == 2 ? (cc ^ (li >> 3)) * 16 : 0);
+    const char* const mb = mts + cb * TS::kMBuf + cc * TS::kMPlanes * BN * TS::kMUnit;
+    constexpr int grp = 32 * T / G;
+    r.H = u32x2{0u, 0u};
+    if constexpr (BITS == 4) {
+      r.L = u32x2{*reinterpret_cast<const uint32_t*>(cr0 + T * SL + 4 * g), 0u};
+    } else {
+      const int sl = T == 0 || T == 3 ? g >> 1 : T == 1 ? (g < 2 ? 2 : 0) : g < 2 ? 1 : 2;
+      r.L = *reinterpret_cast<const u32x2*>(cr0 + sl * SL + 8 * (g & 1));
+      if constexpr (T == 3) r.H = *reinterpret_cast<const u32x2*>(cr0 + 2 * SL + 8 * (g & 1));
+    }
+    if constexpr (KIND == QX_UNIFORM) {
+      const u32x2 v = *reinterpret_cast<const u32x2*>(mb + (grp * BN + row) * 8);
+      r.sp = v.x; r.z0 = v.y;
+    } else if constexpr (KIND == QX_Q4X) {
+      const u32x2 v = *reinterpret_cast<const u32x2*>(mb + row * 8);
+      r.sp = perm(v.x, v.x, grp == 0 ? 0x01000100u : 0x03020302u);
+      r.z0 = 0u;
+      const uint32_t* tp = q4lut + 8 * ((v.y >> (2 * grp)) & 3u);
+      const u32x4 tl = *reinterpret_cast<const u32x4*>(tp), th = *reinterpret_cast<const u32x4*>(tp + 4);
+      r.lut = LutGroup<BITS>{{tl.x, tl.y, tl.z, tl.w}, {th.x, th.y, th.z, th.w}};
+    } else {
+      r.sp = r.z0 = 0u;
+#pragma unroll
+      for (int u = 0; u < TS::kTable / 16; ++u) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(mb + ((grp * (TS::kTable / 16) + u) * BN + row) * 16);
+        r.lut.lo[2 * u] = v.x; r.lut.lo[2 * u + 1] = v.y; r.lut.hi[2 * u] = v.z; r.lut.hi[2 * u + 1] = v.w;
+      }
+    }
+    return r;
+  };
+  // piece j of activation row r sits at position j ^ (r / 2) % 8 of the row: the 16 lanes that
+  // the LDS serves together (of 16 rows, or of 8 rows and two pieces) hit all 64 banks
+  const char* const xl[2] = {xs + (wm * 16 * MT + li) * kXRow + ((g ^ (li >> 1)) & 7) * 16,
+                             xs + (wm * 16 * MT + li) * kXRow + (((4 + g) ^ (li >> 1)) & 7) * 16};
+  h8_t b[2][NT];
+
+  // k-step T of a chunk: the weight fragments are decoded, then the activation fragments
+  // are read one tile ahead of the products. The fences keep that order (left alone, the
+  // scheduler reads a fragment right before its use and hoists more code reads than the
+  // registers hold).
+  auto kstep = [&](auto tc, int cb, int cc) {
+    constexpr int T = decltype(tc)::value;
+    const char* const xb = xl[T % 2] + (T / 2) * TS::kXBuf;
+    h8_t pa = *reinterpret_cast<const h8_t*>(xb);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      b[0][nt] = tile_frag<BITS, KIND, T, true>(read_raw(tc, cb, cc, nt), kc, t1, up, dn, ssh);
+      if constexpr (MT * NT == 32 && (BITS == 3 || KIND != QX_UNIFORM))
+        if (nt % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const h8_t a = pa;
+      if (mt + 1 < MT) pa = *reinterpret_cast<const h8_t*>(xb + 16 * (mt + 1) * kXRow);
+#pragma unroll
+      for (int j = 0; j < NT; ++j)  // weights as rows: a lane ends with four neighbouring columns of Y
+        acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b[0][j], a, acc[mt][j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // With group sums: half h of the chunk in code buffer cb, both k-steps of 16 activation
+  // rows together (a group of 64 spans them; half a group of 128 is summed alone).
+  auto round = [&](auto hc, int cb, int cc) {
+    constexpr int H = decltype(hc)::value;
+    constexpr int GR = G == 32 ? 2 : 1;  // groups of the half chunk
+    float sg[GR][NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const RawFrag<BITS, KIND> r0 = read_raw(std::integral_constant<int, 2 * H>{}, cb, cc, nt);
+      const RawFrag<BITS, KIND> r1 = read_raw(std::integral_constant<int, 2 * H + 1>{}, cb, cc, nt);
+      sg[0][nt] = half_bits_to_float(r0.sp & 0xFFFFu);
+      if constexpr (GR == 2) sg[1][nt] = half_bits_to_float(r1.sp & 0xFFFFu);
+      b[0][nt] = tile_frag<BITS, KIND, 2 * H, false>(r0, kc, t1, up, dn, ssh);
+      b[1][nt] = tile_frag<BITS, KIND, 2 * H + 1, false>(r1, kc, t1, up, dn, ssh);
+      // the reads of later rows, hoisted here, would not fit the registers
+      if constexpr (MT * NT == 32)
+        if (nt % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    const char *const xb = xl[0] + H * TS::kXBuf, *const xc = xl[1] + H * TS::kXBuf;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      const h8_t a0 = *reinterpret_cast<const h8_t*>(xb + 16 * mt * kXRow);
+      const h8_t a1 = *reinterpret_cast<const h8_t*>(xc + 16 * mt * kXRow);
+      const f4_t zero = {0.f, 0.f, 0.f, 0.f};
+      f4_t s0[NT], s1[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) s0[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b[0][nt], zero, 0, 0, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        s1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b[1][nt], GR == 2 ? zero : s0[nt], 0, 0, 0);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        if constexpr (GR == 2) acc[mt][nt] += sg[0][nt] * s0[nt];
+        acc[mt][nt] += sg[GR - 1][nt] * s1[nt];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  if constexpr (KIND == QX_Q4X) stage_q4x_tables(packed + q4x_offsets(n, k).codebook, q4lut);
+  load_codes(0);
+  load_x(0, 0);
+  store_codes(0);
+  load_codes(1);
+  store_x(0);
+  __syncthreads();
+  // Super-round j + 1's codes go to the buffer last read in super-round j - 1; at least one
+  // barrier follows before their first read. Each activation buffer is written one barrier
+  // after its last read.
+  auto k0 = std::integral_constant<int, 0>{};
+  auto k1 = std::integral_constant<int, 1>{};
+  auto k2 = std::integral_constant<int, 2>{};
+  auto k3 = std::integral_constant<int, 3>{};
+  for (int j = 0; j <= last_j; ++j) {
+#pragma unroll
+    for (int cc = 0; cc < SC; ++cc) {
+      const int c = j * SC + cc;
+      if (c < C) {
+        load_x(c, 1);
+        if (cc == 0) {
+          store_codes((j + 1) & 1);
+          load_codes(j + 2);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kSums) {
+          round(k0, j & 1, cc);
+        } else {
+          kstep(k0, j & 1, cc);
+          kstep(k1, j & 1, cc);
+        }
+        store_x(1);
+        __syncthreads();
+        load_x(c + 1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (kSums) {
+          round(k1, j & 1, cc);
+        } else {
+          kstep(k2, j & 1, cc);
+          kstep(k3, j & 1, cc);
+        }
+        store_x(0);
+        __syncthreads();
+      }
+    }
+  }
+
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    if constexpr (!kSums) {  // lane: activation row li, weight rows 4g + r
+      const int row = m0 + (wm * MT + mt) * 16 + li;
+      if (row < m) {
+        const float sr = A8 ? sx[row] : 1.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const int col = n0 + (wn * NT + nt) * 16 + 4 * g;
+          uint32_t v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = float_to_half_bits(A8 ? acc[mt][nt][r] * sr : acc[mt][nt][r]);
+          uint16_t* const dst = Y + (size_t)row * n + col;
+          if (vec) {  // rows of Y start at multiples of 8 bytes (n % 4 == 0)
+            if (col < n) *reinterpret_cast<u32x2*>(dst) = u32x2{v[0] | (v[1] << 16), v[2] | (v[3] << 16)};
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (col + r < n) dst[r] = (uint16_t)v[r];
+          }
+        }
+      }
+    } else {  // lane: weight row li, activation rows 4g + r
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + (wm * MT + mt) * 16 + 4 * g + r;
+        if (row < m) {
+          const float sr = sx[row];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const int col = n0 + (wn * NT + nt) * 16 + li;
+            if (col < n) Y[(size_t)row * n + col] = (uint16_t)float_to_half_bits(sr * acc[mt][nt][r]);
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int BITS, int KIND, int G, bool A8, int MT, int NT, int WM, int SC>
+int launch_cfg(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
+               hipStream_t s) {
+  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC>;
+  static_assert(TS::kLds <= kLdsBytes, "LDS");
+  const int nx = (d->n + TS::BN - 1) / TS::BN, my = (m + TS::BM - 1) / TS::BM;
+  const unsigned blocks = (unsigned)((nx + 7) / 8) * 8u * (unsigned)my;
+  const int vec = d->n % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) & 7u) == 0;
+  hipLaunchKernelGGL((gemm_tile_kernel<BITS, KIND, G, MT, NT, WM, SC, A8>), dim3(blocks), dim3(TS::kThreads), 0,
+                     s, static_cast<const char*>(packed), X, sx, Y, d->n, d->k, m, nx, my, vec);
+  return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;
+}
+
+// Block shapes, as activation x weight rows. Cost of a round of blocks with one, two or
+// three of them on each of the 256 compute units, in us per 32 chunks of k (measured with
+// uniform and codebook-3 g128 weights on 11008x4096, 4096x11008 and 4096x4096, m = 96 to
+// 4096; the sum over rounds reproduces every measured time within 8 %).
+enum Shape { kA, kB, kC, kD, kE, kShapes };
+struct ShapeCost {
+  int bm, bn, mt, nt, wm, sc;
+  float us[3];
+};
+constexpr ShapeCost kShape[kShapes] = {
+    {256, 256, 8, 4, 2, 2, {112.f, 0.f, 0.f}},
+    {128, 256, 8, 4, 1, 1, {80.f, 135.f, 0.f}},
+    {128, 192, 8, 3, 1, 1, {71.f, 121.f, 0.f}},
+    {128, 128, 8, 2, 1, 2, {60.f, 78.f, 0.f}},
+    {64, 128, 4, 2, 1, 2, {41.f, 54.f, 74.f}},
+};
+
+// Formats whose decoding leaves the registers of the 128 x 64 wave tile unspilled.
+template <int BITS, int KIND, int G, bool A8>
+constexpr bool kLight = KIND == QX_UNIFORM ? !A8 : KIND == QX_CODEBOOK && BITS == 3 && G >= 64;
+
+// Shapes that are built: the 128 x 64 wave tiles (A, B) for the light formats and B for
+// codebook-4 g32, whose tables let one block of any shape on a compute unit.
+template <int BITS, int KIND, int G, bool A8>
+constexpr bool built(int s) {
+  if (s == kA) return kLight<BITS, KIND, G, A8> && !A8;
+  if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && BITS == 4 && G == 32);
+  return true;
+}
+
+template <int BITS, int KIND, int G, int S>
+constexpr int per_unit() {  // blocks that fit a compute unit: LDS, and two or three by registers
+  using TS = TileShape<BITS, KIND, G, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc>;
+  constexpr int lds = kLdsBytes / TS::kLds, regs = S == kA ? 1 : S == kE ? 3 : 2;
+  return lds < regs ? lds : regs;
+}
+
+// Cost of the heavier decoders over that of uniform codes on shapes C, D and E (the same
+// sweep): 16-entry tables, tables of 32 or 64 codes, group sums.
+template <int BITS, int KIND, int G, bool A8>
+constexpr float decode_factor() {
+  if (KIND == QX_Q4X) return 1.4f;
+  if (KIND == QX_CODEBOOK)
+    return (BITS == 4 ? (G == 32 ? 1.5f : G == 64 ? 1.35f : 1.2f) : G == 32 ? 1.2f : 1.f) * (A8 ? 1.08f : 1.f);
+  return A8 ? (G == 32 ? 1.36f : 1.1f) : 1.f;
+}
+
+template <int BITS, int KIND, int G, bool A8, int S>
+void consider(const qx_desc* d, int m, float& best, int& shape) {
+  if constexpr (built<BITS, KIND, G, A8>(S)) {
+    constexpr int per = per_unit<BITS, KIND, G, S>();
+    const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
+    const long rest = blocks % (256 * per);
+    const float us = decode_factor<BITS, KIND, G, A8>() *
+                     ((float)(blocks / (256 * per)) * kShape[S].us[per - 1] + (rest ? kShape[S].us[(rest - 1) / 256] : 0.f));
+    if (us < best) {
+      best = us;
+      shape = S;
+    }
+  }
+}
+
+// The same cost for the kernels that took these products before (gemm.hip, gemm_a8.hip),
+// fitted to their times in the sweep:
+//   fp16 activations, uniform: 128 x 256 blocks at 76 us a round from m = 384 (11008x4096
+//     uniform-4 g128 at m = 512 / 1024 / 2048: 77 / 142 / 227 us), 128 x 64 tiles that take
+//     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54);
+//     few tiles are split over k (39 us: 4096 rows up to m = 512);
+//   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
+//     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
+//     122 / 223 here), up to 256 tiles split over k (25 us), 0.05 us a tile up to 512 tiles
+//     of long rows (8-wave blocks);
+//   int8 activations, uniform: 64 x 64 tiles, 0.053 us a tile (11008x4096 uniform-3 g64 at
+//     m = 256 / 512 / 1024 / 2048: 56 / 96 / 164 / 318 us against 64 / 86 / 132 / 247 here),
+//     and 22 us more for rows of up to 64 chunks, which have 4-wave blocks.
+template <int BITS, int KIND, int G, bool A8>
+float other_cost(const qx_desc* d, int m) {
+  const bool wide = d->k > 64 * 128;
+  const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
+  if (KIND != QX_UNIFORM)
+    return (t64 <= 256 ? 25.f : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
+           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? 1.5f : 1.f);
+  if (A8) return (0.053f * (float)t64 + (wide ? 0.f : 22.f)) * (G == 32 ? 1.25f : 1.f);
+  const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
+  if (t128 <= 256) return 39.f;
+  if (m >= 384) return 76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256);
+  const long rest = t128 % 768;
+  return 74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f);
+}
+
+template <int BITS, int KIND, int G, bool A8>
+int pick(const qx_desc* d, int m) {
+  float best = other_cost<BITS, KIND, G, A8>(d, m);
+  int shape = kShapes;
+  consider<BITS, KIND, G, A8, kA>(d, m, best, shape);
+  consider<BITS, KIND, G, A8, kB>(d, m, best, shape);
+  consider<BITS, KIND, G, A8, kC>(d, m, best, shape);
+  consider<BITS, KIND, G, A8, kD>(d, m, best, shape);
+  consider<BITS, KIND, G, A8, kE>(d, m, best, shape);
+  return shape;
+}
+
+template <int BITS, int KIND, int G, bool A8, int S>
+int launch_shape(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
+                 hipStream_t s) {
+  if constexpr (built<BITS, KIND, G, A8>(S))
+    return launch_cfg<BITS, KIND, G, A8, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc>(d, packed, m, X, sx, Y, s);
+  else
+    return QX_E_UNSUPPORTED;
+}
+
+template <int BITS, int KIND, int G, bool A8>
+int run(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y, int shape,
+        hipStream_t s) {
+  switch (shape) {
+    case kA: return launch_shape<BITS, KIND, G, A8, kA>(d, packed, m, X, sx, Y, s);
+    case kB: return launch_shape<BITS, KIND, G, A8, kB>(d, packed, m, X, sx, Y, s);
+    case kC: return launch_shape<BITS, KIND, G, A8, kC>(d, packed, m, X, sx, Y, s);
+    case kD: return launch_shape<BITS, KIND, G, A8, kD>(d, packed, m, X, sx, Y, s);
+    case kE: return launch_shape<BITS, KIND, G, A8, kE>(d, packed, m, X, sx, Y, s);
+    default: return QX_E_UNSUPPORTED;
+  }
+}
+
+}  // namespace
+
+#define QX_TILE_FORMATS(F)                                                              \
+  F(3, 0, 32) F(3, 0, 64) F(3, 0, 128) F(4, 0, 32) F(4, 0, 64) F(4, 0, 128) F(3, 1, 32) \
+  F(3, 1, 64) F(3, 1, 128) F(4, 1, 32) F(4, 1, 64) F(4, 1, 128) F(4, 2, 64)
+
+bool gemm_tile_applies(const qx_desc* d, int m, bool a8) {
+  if (m <= 64) return false;  // one or two activation tiles: gemm.hip, gemm_a8.hip, gemm_skinny.hip
+#define QX_TILE_PICK(B, K, G)                             \
+  if (d->bits == B && d->kind == K && d->group == G)      \
+    return (a8 ? pick<B, K, G, true>(d, m) : pick<B, K, G, false>(d, m)) != kShapes;
+  QX_TILE_FORMATS(QX_TILE_PICK)
+#undef QX_TILE_PICK
+  return false;
+}
+
+int launch_gemm_tile(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
+                     hipStream_t s) {
+#define QX_TILE_RUN(B, K, G)                                                                          \
+  if (d->bits == B && d->kind == K && d->group == G)                                                  \
+    return sx != nullptr ? run<B, K, G, true>(d, packed, m, X, sx, Y, pick<B, K, G, true>(d, m), s)   \
+                         : run<B, K, G, false>(d, packed, m, X, sx, Y, pick<B, K, G, false>(d, m), s);
+  QX_TILE_FORMATS(QX_TILE_RUN)
+#undef QX_TILE_RUN
+  return QX_E_UNSUPPORTED;
+}
+
+}  // namespace qx

@@ -227,6 +227,7 @@ int qx_gemm_a8(const qx_desc* d, const void* packed, int32_t m, const int8_t* Xq
   if (packed == nullptr || Xq == nullptr || sx == nullptr || Y == nullptr) return QX_E_ARG;
   if (!aligned16(packed) || !aligned16(Xq) || (reinterpret_cast<uintptr_t>(sx) & 3u) != 0 || !aligned2(Y))
     return QX_E_ARG;
+  if (qx::gemm_tile_applies(d, m, true)) return qx::launch_gemm_tile(d, packed, m, Xq, sx, Y, stream);
   if (d->kind != QX_UNIFORM)  // table levels are fp16: the fp16 matrix cores on the int8 codes
     return qx::launch_gemm_lut_a8(d, packed, m, Xq, sx, Y, stream);
   if (m == 1 && d->k <= 88 * 128)  // one row: the A8 GEMV (v_dot4 on its staged int8 row)
@@ -252,6 +253,7 @@ int qx_gemm(const qx_desc* d, const void* packed, int32_t m, const uint16_t* X, 
   if (qx::gemv_multi_applies(d, m))  // a few rows: decode every code once, GEMV-style
     return m == 1 ? qx::launch_gemv(d, packed, X, Y, stream)
                   : qx::launch_gemv_multi(d, packed, m, X, Y, stream);
+  if (qx::gemm_tile_applies(d, m, false)) return qx::launch_gemm_tile(d, packed, m, X, nullptr, Y, stream);
   return qx::launch_gemm(d, packed, m, X, Y, stream);
 }
 

@@ -51,6 +51,13 @@ int launch_gemm_lut_a8(const qx_desc* d, const void* packed, int m, const int8_t
 int launch_gemv_a8q(const qx_desc* d, const void* packed, const int8_t* xq, const float* sx, uint16_t* y,
                     hipStream_t s);
 
+// Products of more than 64 rows in large wave tiles (gemm_tile.hip), where gemm_tile_applies
+// expects them to take less time than the kernels above: X fp16 [m][k] with sx null, or the
+// int8 rows of qx_quantize_a8 with their scales.
+bool gemm_tile_applies(const qx_desc* d, int m, bool a8);
+int launch_gemm_tile(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
+                     hipStream_t s);
+
 // Products of at most QX_MULTI_MAX_M rows may run GEMV-style (gemv_multi_applies
 // decides; launch_gemv_multi takes 2 <= m <= QX_MULTI_MAX_M, any k, every kind).
 #ifndef QX_MULTI_MAX_M
