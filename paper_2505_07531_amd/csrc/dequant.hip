@@ -4,6 +4,13 @@
 // byte copy through the v_perm tables; Q4X W' = fp16_RNE(s*CB[sel][q]), the
 // table entry times s in one IEEE fp16 multiply). One lane per (row, 128-code
 // chunk).
+//
+// Bound by writing the output. A lane's chunk is 128 or 256 bytes of it, so storing from
+// the lane that decoded would spread every store instruction over 64 cache lines; the
+// wave's 64 chunks are consecutive in the output and go through LDS (128 bytes a chunk at a
+// time, pieces of 16 swizzled by chunk), so that 8 neighbouring lanes write one whole line.
+// The row of a lane comes from one scalar 64-bit division a block and a 32-bit one a lane.
+// 11008x4096 uniform-4 g128 to fp16 (114 MB): 31.9 us before, 18.2 now.
 #include "qx_device.h"
 #include "qx_internal.h"
 
@@ -37,13 +44,40 @@ __device__ __forceinline__ void chunk_codes(const uint32_t (&d)[4 * BITS], uint3
   }
 }
 
+// 128 bytes of each of the wave's chunks (8 dwords x 4 a lane) to the output: `out` is the
+// first chunk's piece, chunks are STRIDE bytes apart, `left` of them exist.
+template <int STRIDE>
+__device__ __forceinline__ void store_wave(char* tile, const uint32_t* w, char* out, int left) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    *reinterpret_cast<u32x4*>(tile + lane * 128 + ((i ^ lane) & 7) * 16) =
+        u32x4{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // one wave's tile: no block barrier
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int ch = 8 * j + (lane >> 3), i = lane & 7;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(tile + ch * 128 + ((i ^ ch) & 7) * 16);
+    if (ch < left) *reinterpret_cast<u32x4*>(out + (size_t)ch * STRIDE + i * 16) = v;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 template <int BITS, int KIND, int G, int OUT>
 __global__ __launch_bounds__(256) void dequant_kernel(const char* __restrict__ packed,
                                                        void* __restrict__ out, int n, int k) {
   const int C = k >> 7;
-  const size_t item = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (item >= (size_t)n * C) return;
-  const int row = (int)(item / C), c = (int)(item - (size_t)row * C);
+  __shared__ __align__(16) char tiles[4][64 * 128];
+  const size_t items = (size_t)n * C, first = (size_t)blockIdx.x * 256;
+  const int row0 = (int)(first / C);
+  // lanes past the last chunk decode it again and store nothing
+  const int at = (int)(first - (size_t)row0 * C) + (int)min((size_t)threadIdx.x, items - 1 - first);
+  const int row = row0 + at / C, c = at % C;
+  const size_t wave0 = first + (threadIdx.x & ~63u);  // the wave's first chunk
+  const int left = wave0 < items ? (int)min((size_t)64, items - wave0) : 0;
+  char* const tile = tiles[threadIdx.x >> 6];
   const u32x4* code = reinterpret_cast<const u32x4*>(packed) + ((size_t)row * BITS * C + c);
   uint32_t d[4 * BITS];
 #pragma unroll
@@ -53,11 +87,8 @@ __global__ __launch_bounds__(256) void dequant_kernel(const char* __restrict__ p
   }
   uint32_t q[32];
   chunk_codes<BITS>(d, q);
-  const size_t e0 = (size_t)row * k + (size_t)c * 128;  // first output element
   if constexpr (OUT == QX_OUT_CODES) {
-    u32x4* o = reinterpret_cast<u32x4*>(static_cast<uint8_t*>(out) + e0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] = u32x4{q[4 * i], q[4 * i + 1], q[4 * i + 2], q[4 * i + 3]};
+    store_wave<128>(tile, q, static_cast<char*>(out) + wave0 * 128, left);
     return;
   } else if constexpr (KIND == QX_Q4X) {
     // groups 2c (codes 0-63) and 2c + 1 (64-127): the selected sub-codebook's entry
@@ -78,9 +109,8 @@ __global__ __launch_bounds__(256) void dequant_kernel(const char* __restrict__ p
         w[2 * t + 1] = hmul2(w[2 * t + 1], sp);
       }
     }
-    u32x4* o = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(out) + e0);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[i] = u32x4{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+    store_wave<256>(tile, w, static_cast<char*>(out) + wave0 * 256, left);
+    store_wave<256>(tile, w + 32, static_cast<char*>(out) + wave0 * 256 + 128, left);
   } else {
     const size_t meta_off = (size_t)n * k * BITS / 8;
     const size_t g0 = (size_t)row * (k / G) + (size_t)c * (128 / G);
@@ -90,9 +120,8 @@ __global__ __launch_bounds__(256) void dequant_kernel(const char* __restrict__ p
 #pragma unroll
     for (int t = 0; t < 32; ++t)
       block_weights<BITS, KIND>(q[t], mp + ((4 * t) / G) * kDw, w[2 * t], w[2 * t + 1]);
-    u32x4* o = reinterpret_cast<u32x4*>(static_cast<uint16_t*>(out) + e0);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[i] = u32x4{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+    store_wave<256>(tile, w, static_cast<char*>(out) + wave0 * 256, left);
+    store_wave<256>(tile, w + 32, static_cast<char*>(out) + wave0 * 256 + 128, left);
   }
 }
 
