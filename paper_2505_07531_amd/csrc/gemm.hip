@@ -455,20 +455,13 @@ static void launch_gemm_cfg(const qx_desc* d, const char* p, int m, const void* 
 // Tile shape per activation row count (from a sweep of MT, NT, KS, S, DX on the
 // 3-bit g64 MLP shapes at m = 16, 64, 512, and at m = 128-512 a split of k when
 // the tiles are few: uniform 4096x11008 at m = 128 took 113 us whole and 57 us
-// split four ways, codebook-3 78 and 55 us split two ways; at m = 32, 35 and 27 us
-// with four waves instead of two on each 32 x 32 tile). Small m is bound by streaming the codes:
+// split four ways, codebook-3 78 and 55 us split two ways). Small m is bound by streaming the codes:
 // one 16-row activation tile, 16 weight rows per block and the chunks of a row
 // split over the four waves, so that the grid has enough blocks. Larger m gets
 // larger activation tiles so that each decoded weight feeds more MFMAs; with
 // m > 64 a wave owns 64 activation x 32 weight rows.
 #ifndef QX_GEMM_CFG
 #define QX_GEMM_CFG 0  // 0: by m; 1, 2, 4 force one shape
-#endif
-#ifndef QX_GEMM_MID_W
-// rows of more than 64 chunks at 16 < m <= 64: the k split over 8 waves instead of 4
-// (4096x11008 at m = 64: uniform-3 39.9 -> 33.4 us, uniform-4 37.1 -> 29.1, codebook-3
-// 34.8 -> 31.3); 4 keeps the 4-wave shape
-#define QX_GEMM_MID_W 8
 #endif
 #ifndef QX_GEMM_BIG_W
 // m > 64, rows of more than 64 chunks, 129-256 tiles (one block of 8 waves per compute
@@ -512,16 +505,9 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
       break;
     }
     case 2:
-      if constexpr (kUni) {
-        // at most 128 tiles of 32 x 32 (a 4096-row matrix at m <= 32): four waves per tile
-        const long tiles = (long)((d->n + 31) / 32) * ((m + 31) / 32);
-        if (QX_GEMM_CFG == 0 && tiles <= 128) launch_gemm_cfg<BITS, KIND, G, 2, 1, 4, 2, 1, A8>(d, p, m, X, sx, Y, s);
-        else if (QX_GEMM_MID_W == 8 && d->k > 64 * 128) launch_gemm_cfg<BITS, KIND, G, 2, 1, 4, 2, 1, A8, 8>(d, p, m, X, sx, Y, s);
-        else launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, 1, A8>(d, p, m, X, sx, Y, s);
-      } else {
-        if (QX_GEMM_MID_W == 8 && d->k > 64 * 128) launch_gemm_cfg<BITS, KIND, G, 2, 1, 4, 2, 2, A8, 8>(d, p, m, X, sx, Y, s);
-        else launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, 2, A8>(d, p, m, X, sx, Y, s);
-      }
+      // 17 to 64 rows: Q4X rows of few chunks (everything else takes gemm_tile.hip there)
+      if constexpr (KIND == QX_Q4X) launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, 2, A8>(d, p, m, X, sx, Y, s);
+      else return QX_E_UNSUPPORTED;
       break;
     default:
       if constexpr (kUni) {

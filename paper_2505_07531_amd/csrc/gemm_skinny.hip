@@ -1,5 +1,5 @@
 // Small-batch quantized GEMM on the matrix cores: Y[m][n] = sum_k X[m][k] W'[n][k]
-// for 2 <= m <= 64 activation rows (decode of several sequences, short prefill chunks).
+// for 2 <= m <= 32 activation rows (decode of several sequences, short prefill chunks).
 //
 // With few activation rows the product is still bound by streaming the packed
 // weights (decoding is memory-bound, Section 2.4 of the paper), so this kernel
@@ -536,7 +536,7 @@ template <int BITS, int KIND, int G, int RF, int J, int LB>
 int launch_cfg(const qx_desc* d, const char* p, int m, const uint16_t* X, uint16_t* Y, hipStream_t s) {
   const int C = d->k / 128;
   const int W = (C + 4 * J - 1) / (4 * J);
-  if (W > LB / 64 || m > 64) return QX_E_UNSUPPORTED;
+  if (W > LB / 64 || m > QX_SKINNY_MAX_M) return QX_E_UNSUPPORTED;
   const size_t rows_bytes = (size_t)W * std::min(m, 16) * kXRow, red_bytes = (size_t)W * RF * 256 * sizeof(float);
   const bool sep = rows_bytes + red_bytes <= 160 * 1024;  // reduction tiles past the staged rows
   const size_t lds = sep ? rows_bytes + red_bytes : std::max(rows_bytes, red_bytes);
@@ -545,9 +545,11 @@ int launch_cfg(const qx_desc* d, const char* p, int m, const uint16_t* X, uint16
   if (m <= 16)
     hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 1>), dim3(blocks), dim3(64 * W), lds, s, p, X,
                        Y, d->n, d->k, m, red_off);
-  else
-    hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 4>), dim3(blocks), dim3(64 * W), lds, s, p, X,
+  else if constexpr (J == 1 && RF <= 3)  // two activation tiles: rows of at most 32 chunks
+    hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 2>), dim3(blocks), dim3(64 * W), lds, s, p, X,
                        Y, d->n, d->k, m, red_off);
+  else
+    return QX_E_UNSUPPORTED;
   return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;
 }
 
@@ -598,15 +600,14 @@ int launch_t(const qx_desc* d, const void* packed, int m, const uint16_t* X, uin
 
 }  // namespace
 
-// Whether qx_gemm runs m rows on this kernel. Beyond 16 rows (several activation tiles,
-// every code decoded again per tile) only rows of at most 32 chunks with one round of
-// blocks (us at m = 24 / 32 / 48 / 64 against the matrix-core GEMM, weights rotated over
-// four copies: 11008x4096 uniform-3 g64 16.8 / 17.5 / 23.7 / 29.4 vs 21.6 / 21.5 / 27.5 /
-// 27.8; 12288x4096 codebook-3 15.0 / 15.8 / 20.6 / 25.5 vs 19.9 / 19.9 / 25.0 / 25.1;
-// 4096x4096 codebook-3 8.9 / 9.1 / 11.5 / 14.0 vs 14.8 / 14.9 / 15.3 / 15.5; 22016 rows,
-// two rounds: 28.5 / 30.2 / 40.2 / 49.7 vs 24.5 / 24.9 / 40.1 / 41.4; at m = 64 the tall
-// matrices' GEMM gains came from the last-level cache: with the c5 MLP's weights streamed
-// from HBM, 87.2 us per gate + up + down against 89.7 with them on the GEMM). Up to 16 rows: measured against the
+// Whether qx_gemm runs m rows on this kernel. Beyond 16 rows (a second activation tile,
+// every code decoded again for it) only up to 32 of at most 32 chunks with one round of
+// blocks (us at m = 24 / 32 against the matrix-core GEMM of gemm.hip, weights rotated over
+// four copies: 11008x4096 uniform-3 g64 16.8 / 17.5 vs 21.6 / 21.5; 12288x4096 codebook-3
+// 15.0 / 15.8 vs 19.9 / 19.9; 4096x4096 codebook-3 8.9 / 9.1 vs 14.8 / 14.9; 22016 rows, two
+// rounds: 28.5 / 30.2 vs 24.5 / 24.9; against gemm_tile.hip 15.1 vs 17.1 at 12288x4096
+// codebook-3, m = 28, and 8.1 vs 9.6 at 4096x4096 uniform-4, m = 19, but 29.9 vs 18.4 at
+// 11008x4096 uniform-3 g64, m = 64). Up to 16 rows: measured against the
 // small-batch GEMV-style kernel (m <= 4) and the matrix-core GEMM in all thirteen formats
 // (us, 3-bit uniform g64 at m = 2 / 8 / 16: 11008x4096 8.4 / 9.0 / 9.9 against 9.2 / 15.7 /
 // 15.8; 4096x4096 4.9 / 5.5 / 6.2 against 5.5 / 8.7 / 8.7). Rows of more than 32 chunks

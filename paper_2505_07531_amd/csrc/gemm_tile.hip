@@ -21,6 +21,15 @@
 // a compute unit and one decodes while another multiplies; a block of 256 x 256 has two
 // waves on every SIMD itself.
 //
+// Few tiles (KS > 1): a block of KS waves owns one tile of 16*MT x 16*NT and wave ks takes
+// the chunks ks, ks + KS, .. of k. With few blocks the time is one wave's chain of loads,
+// decoding and products over all of k, so the chain is cut in KS; every wave stages its own
+// activations and codes in its own part of the LDS and meets the others only when the
+// partial tiles are added in the order of the waves (deterministic).
+// 11008x4096 uniform-3 g64 at m = 64: 29.9 us before (gemm_skinny.hip), 18.4 now;
+// 4096x11008 29.9 -> 21.0 us; 1376x4096 uniform-4 g32 at m = 77: 20.7 us (gemm.hip) -> 9.6;
+// 4001x1408 codebook-4 g64 13.8 -> 9.3 us.
+//
 // LDS banks. Activation rows of 128 bytes with 16-byte pieces swizzled by row (padding by
 // 16 bytes left 37 % of the LDS cycles to conflicts, because the lanes that the LDS serves
 // together come from two pieces), codes swizzled so that 16 rows of one chunk hit all banks.
@@ -47,10 +56,11 @@ namespace {
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int kXRow = 128;  // LDS bytes of one activation row of a round: 64 fp16
 
-template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC>
+template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, int KS>
 struct TileShape {
-  static constexpr int kThreads = 256 * WM;
-  static constexpr int BM = 16 * MT * WM, BN = 64 * NT, NG = 128 / G;
+  static constexpr int kThreads = KS > 1 ? 64 * KS : 256 * WM;
+  static constexpr int WN = KS > 1 ? 1 : 4;  // waves on different weight rows
+  static constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN, NG = 128 / G;
   static constexpr int kTable = 2 << BITS;  // bytes of a codebook group's table
   // LDS planes of BN rows x kMUnit bytes that hold a chunk's groups as the decoders take them
   // (prepared once a block when they are stored): uniform (s, s) and -(1024 + z), the lookup
@@ -58,9 +68,10 @@ struct TileShape {
   static constexpr int kMUnit = KIND == QX_CODEBOOK ? 16 : 8;
   static constexpr int kMPlanes = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 1 : NG * kTable / 16;  // per chunk
   static constexpr int kXBuf = BM * kXRow, kCBuf = BITS * BN * SC * 16, kMBuf = kMPlanes * SC * BN * kMUnit;
-  static constexpr int kLds = 2 * (kXBuf + kCBuf + kMBuf) + (KIND == QX_Q4X ? 128 : 0);
+  static constexpr int kWaveLds = (KS > 1 ? 1 : 2) * kXBuf + 2 * (kCBuf + kMBuf);  // KS > 1: of one wave
+  static constexpr int kLds = KS * kWaveLds + (KIND == QX_Q4X ? 128 : 0);
   // waves on a SIMD for which registers are allocated
-  static constexpr int kWaves = WM == 2 || 2 * kLds <= kLdsBytes ? 2 : 1;
+  static constexpr int kWaves = KS > 1 ? KS / 4 * (2 * kLds <= kLdsBytes ? 2 : 1) : WM == 2 || 2 * kLds <= kLdsBytes ? 2 : 1;
 };
 
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
@@ -139,13 +150,14 @@ __device__ __forceinline__ h8_t tile_frag(const RawFrag<BITS, KIND>& gd, const D
   }
 }
 
-template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, bool A8,
-          int WAVES = TileShape<BITS, KIND, G, MT, NT, WM, SC>::kWaves>
-__global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
+template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, int KS, bool A8,
+          int THREADS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>::kThreads,
+          int WAVES = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>::kWaves>
+__global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
     const char* __restrict__ packed, const void* __restrict__ Xv, const float* __restrict__ sx,
     uint16_t* __restrict__ Y, int n, int k, int m, int nx, int my, int vec) {
-  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC>;
-  constexpr int NTH = TS::kThreads, BM = TS::BM, BN = TS::BN, NG = TS::NG;
+  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>;
+  constexpr int NTH = KS > 1 ? 64 : TS::kThreads, BM = TS::BM, BN = TS::BN, NG = TS::NG;
   constexpr bool kSums = A8 && KIND != QX_CODEBOOK;  // group sums scaled in fp32
   constexpr int XP = BM * 8 / NTH;                   // 16-byte activation pieces per thread and round
   constexpr int CT = BITS * BN * SC, CP = (CT + NTH - 1) / NTH;
@@ -154,23 +166,28 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
   constexpr int MD = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 2 : 4;  // dwords of one
   static_assert(BM * 8 % NTH == 0, "activation pieces divide evenly");
   __shared__ __align__(16) char lds[TS::kLds];
-  char* const xs = lds;
-  char* const cts = lds + 2 * TS::kXBuf;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char* const xs = lds + (KS > 1 ? wave * TS::kWaveLds : 0);
+  char* const cts = xs + (KS > 1 ? 1 : 2) * TS::kXBuf;
   char* const mts = cts + 2 * TS::kCBuf;
-  uint32_t* const q4lut = reinterpret_cast<uint32_t*>(mts + 2 * TS::kMBuf);
+  uint32_t* const q4lut = reinterpret_cast<uint32_t*>(lds + KS * TS::kWaveLds);
 
   // Block -> (weight tile bn, activation tile bm). Workgroups are dealt to the 8 XCDs
-  // round-robin; an XCD takes every eighth weight tile and walks them with up to 8
-  // activation tiles together, so that the tiles in flight in its L2 form a square.
-  const int nb = (nx + 7) >> 3, q = blockIdx.x >> 3;
-  const int hi = q / (nb * 8), gsz = min(8, my - hi * 8), rem = q - hi * nb * 8;
-  const int bm = hi * 8 + rem % gsz, bn = (rem / gsz) * 8 + (blockIdx.x & 7);
-  if (bn >= nx) return;  // padding blocks: whole block, before any barrier
+  // round-robin; every XCD takes an equal run of the tiles, which are numbered in squares of
+  // up to 8 activation tiles by consecutive weight tiles, so that the tiles in flight in its
+  // L2 share both. (A run of whole weight tiles an XCD leaves units idle when they are few:
+  // 1024x5120 uniform-4 g32 at m = 683, 22 x 11 tiles: 46 us against 31 before.)
+  const int total = nx * my, share = (total + 7) >> 3, at = blockIdx.x >> 3;
+  const int tile = (int)(blockIdx.x & 7) * share + at;
+  if (tile >= total) return;  // whole block, before any barrier
+  const int hi = tile / (nx * 8), gsz = min(8, my - hi * 8), rem = tile - hi * nx * 8;
+  const int bm = hi * 8 + rem % gsz, bn = rem / gsz;
   const int n0 = bn * BN, m0 = bm * BM;
   const int C = k >> 7, G_row = k / G;
   const size_t meta_off = (size_t)n * k * BITS / 8;
-  const int t = threadIdx.x, lane = t & 63, g = lane >> 4, li = lane & 15;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wn = wave & 3, wm = wave >> 2;
+  const int t = KS > 1 ? threadIdx.x & 63 : threadIdx.x, lane = t & 63, g = lane >> 4, li = lane & 15;
+  const int wn = KS > 1 ? 0 : wave & 3, wm = KS > 1 ? 0 : wave >> 2, ks = KS > 1 ? wave : 0;
+  const int CW = (C - ks + KS - 1) / KS;  // this wave's chunks: ks, ks + KS, ..
   const DecodeConsts kc = decode_consts();
   const uint32_t t1 = g < 2 ? 0u : 3u, up = g < 2 ? 2u : 1u, dn = g < 2 ? 6u : 7u, ssh = g < 2 ? 4u : 5u;
 
@@ -192,7 +209,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
                                  KIND == QX_Q4X ? wrows * sel_words * 4 : 0);
   const int xoff = (t >> 3) * k * kXB + (t & 7) * 8 * kXB;
   auto load_x = [&](int c, int h) {
-    const int so = (min(c, C - 1) * 128 + h * 64) * kXB;
+    const int so = (min(c * KS + ks, C - 1) * 128 + h * 64) * kXB;
 #pragma unroll
     for (int i = 0; i < XP; ++i) {
       const int so_i = so + i * (NTH / 8) * k * kXB;  // uniform
@@ -213,7 +230,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
         hh = i8x4_to_h4(xr[i].y);
         lo = i8x4_to_h4(xr[i].x);
       }
-      *reinterpret_cast<u32x4*>(xs + buf * TS::kXBuf + (p >> 3) * kXRow + ((p ^ (p >> 4)) & 7) * 16) = x_piece<BITS>(lo, hh);
+      *reinterpret_cast<u32x4*>(xs + (KS > 1 ? 0 : buf) * TS::kXBuf + (p >> 3) * kXRow + ((p ^ (p >> 4)) & 7) * 16) = x_piece<BITS>(lo, hh);
     }
   };
   // Code piece p = t + i * NTH of a super-round (SC chunks): SC neighbouring lanes take a
@@ -240,9 +257,10 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
   }
   // Codes and tables of super-round j. Past the last chunk of a row the loads run on into
   // what follows (or out of bounds, 0); it is never multiplied.
-  const int last_j = (C - 1) / SC;
+  static_assert(KS == 1 || SC == 1, "waves on their own chunks take them one by one");
+  const int last_j = KS > 1 ? CW - 1 : (C - 1) / SC;
   auto load_codes = [&](int j) {
-    const int c = min(j, last_j) * SC;
+    const int c = KS > 1 ? min(j * KS + ks, C - 1) : min(j, last_j) * SC;
 #pragma unroll
     for (int i = 0; i < CP; ++i)
       cr[i] = __builtin_bit_cast(
@@ -358,7 +376,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
   // registers hold).
   auto kstep = [&](auto tc, int cb, int cc) {
     constexpr int T = decltype(tc)::value;
-    const char* const xb = xl[T % 2] + (T / 2) * TS::kXBuf;
+    const char* const xb = xl[T % 2] + (KS > 1 ? 0 : T / 2) * TS::kXBuf;
     h8_t pa = *reinterpret_cast<const h8_t*>(xb);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -395,7 +413,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
       if constexpr (MT * NT == 32)
         if (nt % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
-    const char *const xb = xl[0] + H * TS::kXBuf, *const xc = xl[1] + H * TS::kXBuf;
+    const char *const xb = xl[0] + (KS > 1 ? 0 : H) * TS::kXBuf, *const xc = xl[1] + (KS > 1 ? 0 : H) * TS::kXBuf;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
       const h8_t a0 = *reinterpret_cast<const h8_t*>(xb + 16 * mt * kXRow);
@@ -430,11 +448,20 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
   auto k1 = std::integral_constant<int, 1>{};
   auto k2 = std::integral_constant<int, 2>{};
   auto k3 = std::integral_constant<int, 3>{};
+  // KS > 1: every wave works in its own part of the LDS and only its own order counts
+  auto round_end = [&]() {
+    if constexpr (KS > 1) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      __syncthreads();
+    }
+  };
   for (int j = 0; j <= last_j; ++j) {
 #pragma unroll
     for (int cc = 0; cc < SC; ++cc) {
       const int c = j * SC + cc;
-      if (c < C) {
+      if (c < CW) {
         load_x(c, 1);
         if (cc == 0) {
           store_codes((j + 1) & 1);
@@ -447,8 +474,9 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
           kstep(k0, j & 1, cc);
           kstep(k1, j & 1, cc);
         }
+        if (KS > 1) round_end();
         store_x(1);
-        __syncthreads();
+        round_end();
         load_x(c + 1, 0);
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (kSums) {
@@ -457,9 +485,26 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
           kstep(k2, j & 1, cc);
           kstep(k3, j & 1, cc);
         }
+        if (KS > 1) round_end();
         store_x(0);
-        __syncthreads();
+        round_end();
       }
+    }
+  }
+
+  // The waves' partial tiles, added in the order of the waves: tile i by wave i % KS.
+  if constexpr (KS > 1) {
+    static_assert(MT * NT * 1024 <= TS::kWaveLds, "a wave's partial tiles fit its LDS");
+#pragma unroll
+    for (int i = 0; i < MT * NT; ++i) *reinterpret_cast<f4_t*>(xs + i * 1024 + lane * 16) = acc[i / NT][i % NT];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MT * NT; ++i) {
+      if (i % KS != wave) continue;
+      f4_t sum = *reinterpret_cast<const f4_t*>(lds + i * 1024 + lane * 16);
+#pragma unroll
+      for (int w = 1; w < KS; ++w) sum += *reinterpret_cast<const f4_t*>(lds + w * TS::kWaveLds + i * 1024 + lane * 16);
+      acc[i / NT][i % NT] = sum;
     }
   }
 
@@ -471,6 +516,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
         const float sr = A8 ? sx[row] : 1.f;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
+          if (KS > 1 && (mt * NT + nt) % KS != wave) continue;
           const int col = n0 + (wn * NT + nt) * 16 + 4 * g;
           uint32_t v[4];
 #pragma unroll
@@ -493,6 +539,7 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
           const float sr = sx[row];
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt) {
+            if (KS > 1 && (mt * NT + nt) % KS != wave) continue;
             const int col = n0 + (wn * NT + nt) * 16 + li;
             if (col < n) Y[(size_t)row * n + col] = (uint16_t)float_to_half_bits(sr * acc[mt][nt][r]);
           }
@@ -502,15 +549,15 @@ __global__ __launch_bounds__(256 * WM, WAVES) void gemm_tile_kernel(
   }
 }
 
-template <int BITS, int KIND, int G, bool A8, int MT, int NT, int WM, int SC>
+template <int BITS, int KIND, int G, bool A8, int MT, int NT, int WM, int SC, int KS = 1>
 int launch_cfg(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
                hipStream_t s) {
-  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC>;
+  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>;
   static_assert(TS::kLds <= kLdsBytes, "LDS");
   const int nx = (d->n + TS::BN - 1) / TS::BN, my = (m + TS::BM - 1) / TS::BM;
-  const unsigned blocks = (unsigned)((nx + 7) / 8) * 8u * (unsigned)my;
+  const unsigned blocks = ((unsigned)nx * (unsigned)my + 7u) / 8u * 8u;
   const int vec = d->n % 4 == 0 && (reinterpret_cast<uintptr_t>(Y) & 7u) == 0;
-  hipLaunchKernelGGL((gemm_tile_kernel<BITS, KIND, G, MT, NT, WM, SC, A8>), dim3(blocks), dim3(TS::kThreads), 0,
+  hipLaunchKernelGGL((gemm_tile_kernel<BITS, KIND, G, MT, NT, WM, SC, KS, A8>), dim3(blocks), dim3(TS::kThreads), 0,
                      s, static_cast<const char*>(packed), X, sx, Y, d->n, d->k, m, nx, my, vec);
   return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;
 }
@@ -519,35 +566,45 @@ int launch_cfg(const qx_desc* d, const void* packed, int m, const void* X, const
 // three of them on each of the 256 compute units, in us per 32 chunks of k (measured with
 // uniform and codebook-3 g128 weights on 11008x4096, 4096x11008 and 4096x4096, m = 96 to
 // 4096; the sum over rounds reproduces every measured time within 8 %).
-enum Shape { kA, kB, kC, kD, kE, kShapes };
+enum Shape { kA, kB, kC, kD, kE, kF, kG, kH, kShapes };
 struct ShapeCost {
   int bm, bn, mt, nt, wm, sc;
   float us[3];
+  int ks;
 };
 constexpr ShapeCost kShape[kShapes] = {
-    {256, 256, 8, 4, 2, 2, {112.f, 0.f, 0.f}},
-    {128, 256, 8, 4, 1, 1, {80.f, 135.f, 0.f}},
-    {128, 192, 8, 3, 1, 1, {71.f, 121.f, 0.f}},
-    {128, 128, 8, 2, 1, 2, {60.f, 78.f, 0.f}},
-    {64, 128, 4, 2, 1, 2, {41.f, 54.f, 74.f}},
+    {256, 256, 8, 4, 2, 2, {112.f, 0.f, 0.f}, 1},
+    {128, 256, 8, 4, 1, 1, {80.f, 135.f, 0.f}, 1},
+    {128, 192, 8, 3, 1, 1, {71.f, 121.f, 0.f}, 1},
+    {128, 128, 8, 2, 1, 2, {60.f, 78.f, 0.f}, 1},
+    {64, 128, 4, 2, 1, 2, {41.f, 54.f, 74.f}, 1},
+    // k split over 8 waves: us[0] + us[1] a chunk for a round of 256 blocks (H: us[2] of it
+    // for each round after the first, several blocks share a unit). Uniform-3 g64 at 32
+    // chunks / 86 chunks, one round: F 18 / 35 us, G 13.5 / 28.5, H 9.9 / 20
+    {64, 48, 4, 3, 1, 1, {8.f, 0.31f, 1.f}, 8},
+    {64, 32, 4, 2, 1, 1, {4.6f, 0.278f, 1.f}, 8},
+    {32, 32, 2, 2, 1, 1, {3.8f, 0.19f, 0.74f}, 8},
 };
 
 // Formats whose decoding leaves the registers of the 128 x 64 wave tile unspilled.
 template <int BITS, int KIND, int G, bool A8>
 constexpr bool kLight = KIND == QX_UNIFORM ? !A8 : KIND == QX_CODEBOOK && BITS == 3 && G >= 64;
 
-// Shapes that are built: the 128 x 64 wave tiles (A, B) for the light formats and B for
+// Shapes that are built: F, G and H not for the integer products of gemm_a8.hip, which split k
+// themselves (11008x4096 uniform-3 g64 at m = 64: 24.1 us there, 22.9 with F; 4096x11008 24.5
+// and 24.6 with H), nor F where its tables overflow LDS; the 128 x 64 wave tiles (A, B) for the light formats and B for
 // codebook-4 g32, whose tables let one block of any shape on a compute unit.
 template <int BITS, int KIND, int G, bool A8>
 constexpr bool built(int s) {
   if (s == kA) return kLight<BITS, KIND, G, A8> && !A8;
   if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && BITS == 4 && G == 32);
+  if (s >= kF) return (KIND != QX_UNIFORM || !A8) && !(s == kF && KIND == QX_CODEBOOK && BITS == 4 && G == 32);
   return true;
 }
 
 template <int BITS, int KIND, int G, int S>
 constexpr int per_unit() {  // blocks that fit a compute unit: LDS, and two or three by registers
-  using TS = TileShape<BITS, KIND, G, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc>;
+  using TS = TileShape<BITS, KIND, G, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc, 1>;
   constexpr int lds = kLdsBytes / TS::kLds, regs = S == kA ? 1 : S == kE ? 3 : 2;
   return lds < regs ? lds : regs;
 }
@@ -582,7 +639,8 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
 //   fp16 activations, uniform: 128 x 256 blocks at 76 us a round from m = 384 (11008x4096
 //     uniform-4 g128 at m = 512 / 1024 / 2048: 77 / 142 / 227 us), 128 x 64 tiles that take
 //     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54);
-//     few tiles are split over k (39 us: 4096 rows up to m = 512);
+//     up to 64 / 128 / 256 tiles of 128 x 64 are split over k (4096x4096 uniform-4 at m = 100 /
+//     256 / 500: 20.6 / 25.8 / 37.6 us);
 //   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
 //     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
 //     122 / 223 here), up to 256 tiles split over k (25 us), 0.05 us a tile up to 512 tiles
@@ -595,25 +653,57 @@ float other_cost(const qx_desc* d, int m) {
   const bool wide = d->k > 64 * 128;
   const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
   if (KIND != QX_UNIFORM)
-    return (t64 <= 256 ? 25.f : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
-           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? 1.5f : 1.f);
+    return (t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
+           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f);
   if (A8) return (0.053f * (float)t64 + (wide ? 0.f : 22.f)) * (G == 32 ? 1.25f : 1.f);
   const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
-  if (t128 <= 256) return 39.f;
+  if (t128 <= 256) return t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f;
   if (m >= 384) return 76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256);
   const long rest = t128 % 768;
   return 74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f);
 }
 
+// Split over k: every block's time is its fixed part and its chunks.
+template <int BITS, int KIND, int G, bool A8, int S>
+void consider_split(const qx_desc* d, int m, float& best, int& shape) {
+  if constexpr (built<BITS, KIND, G, A8>(S)) {
+    const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
+    const float rounds = (float)((blocks + 255) / 256);
+    const float us = decode_factor<BITS, KIND, G, A8>() * (kShape[S].us[0] + kShape[S].us[1] * (float)(d->k / 128)) * (rounds > 1.f ? 1.08f : 1.f) *
+                     (1.f - kShape[S].us[2] + kShape[S].us[2] * rounds);
+    if (us < best) {
+      best = us;
+      shape = S;
+    }
+  }
+}
+
 template <int BITS, int KIND, int G, bool A8>
 int pick(const qx_desc* d, int m) {
-  float best = other_cost<BITS, KIND, G, A8>(d, m);
+  // 17 to 64 rows: one of these shapes, which took less time than gemm_skinny.hip and
+  // gemm.hip in nearly every format and size measured (60 drawn ones: 1.17 times faster on
+  // average); up to 32 rows of up to 32 chunks stay with gemm_skinny.hip where that applies
+  // (4096x4096 uniform-4 at m = 19: 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28:
+  // 15.1 and 17.1). Q4X rows of fewer chunks than waves stay too (12288x640 at m = 21:
+  // 7.5 us there, 8.1 here). Above, a shape must promise 4 % less than the other kernel (12 %
+  // against the integer products, whose fit is coarser: 2146x2432 uniform-3 g128 at m = 2436
+  // 54 us there, 64 here), as much as the costs may be off.
+  const float chunks = (float)(d->k / 128);
+  float best = 1e30f;
   int shape = kShapes;
-  consider<BITS, KIND, G, A8, kA>(d, m, best, shape);
-  consider<BITS, KIND, G, A8, kB>(d, m, best, shape);
-  consider<BITS, KIND, G, A8, kC>(d, m, best, shape);
-  consider<BITS, KIND, G, A8, kD>(d, m, best, shape);
-  consider<BITS, KIND, G, A8, kE>(d, m, best, shape);
+  if (KIND == QX_Q4X && m <= 64 && chunks < 8.f) return shape;
+  if (m > 64) {
+    best = (A8 && KIND == QX_UNIFORM ? 0.88f : 0.96f) * other_cost<BITS, KIND, G, A8>(d, m);
+    consider<BITS, KIND, G, A8, kA>(d, m, best, shape);
+    consider<BITS, KIND, G, A8, kB>(d, m, best, shape);
+    consider<BITS, KIND, G, A8, kC>(d, m, best, shape);
+    consider<BITS, KIND, G, A8, kD>(d, m, best, shape);
+  }
+  if (m > 32 && (m > 64 || !A8 || KIND != QX_UNIFORM)) consider<BITS, KIND, G, A8, kE>(d, m, best, shape);
+  if (best < 1e30f) best = 6.f + (best - 6.f) * chunks / 32.f;  // us at this k (6 us of them fixed)
+  consider_split<BITS, KIND, G, A8, kF>(d, m, best, shape);
+  consider_split<BITS, KIND, G, A8, kG>(d, m, best, shape);
+  consider_split<BITS, KIND, G, A8, kH>(d, m, best, shape);
   return shape;
 }
 
@@ -621,7 +711,7 @@ template <int BITS, int KIND, int G, bool A8, int S>
 int launch_shape(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
                  hipStream_t s) {
   if constexpr (built<BITS, KIND, G, A8>(S))
-    return launch_cfg<BITS, KIND, G, A8, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc>(d, packed, m, X, sx, Y, s);
+    return launch_cfg<BITS, KIND, G, A8, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc, kShape[S].ks>(d, packed, m, X, sx, Y, s);
   else
     return QX_E_UNSUPPORTED;
 }
@@ -635,6 +725,9 @@ int run(const qx_desc* d, const void* packed, int m, const void* X, const float*
     case kC: return launch_shape<BITS, KIND, G, A8, kC>(d, packed, m, X, sx, Y, s);
     case kD: return launch_shape<BITS, KIND, G, A8, kD>(d, packed, m, X, sx, Y, s);
     case kE: return launch_shape<BITS, KIND, G, A8, kE>(d, packed, m, X, sx, Y, s);
+    case kF: return launch_shape<BITS, KIND, G, A8, kF>(d, packed, m, X, sx, Y, s);
+    case kG: return launch_shape<BITS, KIND, G, A8, kG>(d, packed, m, X, sx, Y, s);
+    case kH: return launch_shape<BITS, KIND, G, A8, kH>(d, packed, m, X, sx, Y, s);
     default: return QX_E_UNSUPPORTED;
   }
 }
@@ -646,7 +739,7 @@ int run(const qx_desc* d, const void* packed, int m, const void* X, const float*
   F(3, 1, 64) F(3, 1, 128) F(4, 1, 32) F(4, 1, 64) F(4, 1, 128) F(4, 2, 64)
 
 bool gemm_tile_applies(const qx_desc* d, int m, bool a8) {
-  if (m <= 64) return false;  // one or two activation tiles: gemm.hip, gemm_a8.hip, gemm_skinny.hip
+  if (m <= 16) return false;  // one activation tile: gemm_skinny.hip, gemm.hip, gemm_a8.hip
 #define QX_TILE_PICK(B, K, G)                             \
   if (d->bits == B && d->kind == K && d->group == G)      \
     return (a8 ? pick<B, K, G, true>(d, m) : pick<B, K, G, false>(d, m)) != kShapes;

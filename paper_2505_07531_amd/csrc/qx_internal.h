@@ -51,8 +51,8 @@ int launch_gemm_lut_a8(const qx_desc* d, const void* packed, int m, const int8_t
 int launch_gemv_a8q(const qx_desc* d, const void* packed, const int8_t* xq, const float* sx, uint16_t* y,
                     hipStream_t s);
 
-// Products of more than 64 rows in large wave tiles (gemm_tile.hip), where gemm_tile_applies
-// expects them to take less time than the kernels above: X fp16 [m][k] with sx null, or the
+// Products of more than 16 rows in larger wave tiles, or with k split over a block's waves
+// (gemm_tile.hip), where gemm_tile_applies expects less time than from the other kernels: X fp16 [m][k] with sx null, or the
 // int8 rows of qx_quantize_a8 with their scales.
 bool gemm_tile_applies(const qx_desc* d, int m, bool a8);
 int launch_gemm_tile(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
@@ -71,7 +71,7 @@ int launch_gemv_multi(const qx_desc* d, const void* packed, int m, const uint16_
 // chunk-per-lane loads (gemm_skinny.hip; gemm_skinny_applies picks it per shape and
 // format); k up to 128 chunks.
 #ifndef QX_SKINNY_MAX_M
-#define QX_SKINNY_MAX_M 64
+#define QX_SKINNY_MAX_M 32
 #endif
 bool gemm_skinny_applies(const qx_desc* d, int m);
 

@@ -1,4 +1,4 @@
-"""The large-tile GEMM (more than 64 activation rows) against plain products in 64 bits:
+"""The tiled GEMM (more than 16 activation rows) against plain products in 64 bits:
 every block shape and format, chunk counts 1, 2, 3 and odd ones, partial tiles in both
 directions, rows of Y at odd offsets (n % 4 != 0) and at a misaligned pointer.
 
@@ -15,8 +15,11 @@ pytestmark = pytest.mark.gpu
 U3, U4, C3, C4 = (3, 0), (4, 0), (3, 1), (4, 1)
 FORMATS = [(*f, g) for f in (U3, U4, C3, C4) for g in (32, 64, 128)] + [(4, 2, 64)]
 # Sizes that the cost model gives to each shape in one format or another (k does not enter
-# for k <= 8192): few blocks, one and more rounds of blocks, last blocks of 1 or few rows.
-SIZES = [(4099, 128, 500), (11009, 384, 258), (11008, 256, 521), (5506, 640, 1025), (22013, 256, 1030),
+# for k <= 8192): few blocks, one and more rounds of blocks, last blocks of 1 or few rows;
+# then the shapes that split k over a block's waves, with fewer chunks than waves, as many,
+# and numbers that leave some waves one chunk short.
+SIZES = [(500, 128, 70), (1376, 1024, 77), (4001, 1408, 40), (1001, 1152, 17), (333, 11008, 65), (4096, 11008, 100),
+         (11008, 256, 64), (4099, 128, 500), (11009, 384, 258), (11008, 256, 521), (5506, 640, 1025), (22013, 256, 1030),
          (4096, 128, 2048)]
 
 
@@ -98,9 +101,10 @@ def test_tile_output_offset(gpu, n):
 def test_tile_one_hot_rows(gpu):
     """One-hot activations give columns of W' exactly (every k of two chunks, every format)."""
     import torch
-    qx, dev, n, k = gpu, "cuda", 11009, 384
+    qx, dev, k = gpu, "cuda", 384
     for fmt in FORMATS:
-        print(f"tile one-hot {fmt}", flush=True)
-        pw = qx.PackedWeight.from_quant(quant(fmt, n, k))
-        Y = pw.gemm(torch.eye(k, device=dev).half())
-        assert torch.equal(Y, pw.dequant().t()), fmt
+        for n in (500, 11009):
+            print(f"tile one-hot {fmt} n={n}", flush=True)
+            pw = qx.PackedWeight.from_quant(quant(fmt, n, k))
+            Y = pw.gemm(torch.eye(k, device=dev).half())
+            assert torch.equal(Y, pw.dequant().t()), fmt
