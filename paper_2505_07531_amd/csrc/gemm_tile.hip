@@ -47,32 +47,12 @@
 // 128) is scaled by its s in fp32: at most 64 * 15 * 127 for uniform codes, exact in fp32.
 #include <type_traits>
 
+#include "gemm_tile_plan.h"
 #include "qx_device.h"
-#include "qx_internal.h"
 
 namespace qx {
+using namespace tile;
 namespace {
-
-constexpr int kLdsBytes = 160 * 1024;
-constexpr int kXRow = 128;  // LDS bytes of one activation row of a round: 64 fp16
-
-template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, int KS>
-struct TileShape {
-  static constexpr int kThreads = KS > 1 ? 64 * KS : 256 * WM;
-  static constexpr int WN = KS > 1 ? 1 : 4;  // waves on different weight rows
-  static constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN, NG = 128 / G;
-  static constexpr int kTable = 2 << BITS;  // bytes of a codebook group's table
-  // LDS planes of BN rows x kMUnit bytes that hold a chunk's groups as the decoders take them
-  // (prepared once a block when they are stored): uniform (s, s) and -(1024 + z), the lookup
-  // tables of 8 entries, or the Q4X scales and selectors
-  static constexpr int kMUnit = KIND == QX_CODEBOOK ? 16 : 8;
-  static constexpr int kMPlanes = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 1 : NG * kTable / 16;  // per chunk
-  static constexpr int kXBuf = BM * kXRow, kCBuf = BITS * BN * SC * 16, kMBuf = kMPlanes * SC * BN * kMUnit;
-  static constexpr int kWaveLds = (KS > 1 ? 1 : 2) * kXBuf + 2 * (kCBuf + kMBuf);  // KS > 1: of one wave
-  static constexpr int kLds = KS * kWaveLds + (KIND == QX_Q4X ? 128 : 0);
-  // waves on a SIMD for which registers are allocated
-  static constexpr int kWaves = KS > 1 ? KS / 4 * (2 * kLds <= kLdsBytes ? 2 : 1) : WM == 2 || 2 * kLds <= kLdsBytes ? 2 : 1;
-};
 
 typedef __amdgpu_buffer_rsrc_t BufferRsrc;
 __device__ __forceinline__ BufferRsrc buffer(const void* p, int bytes) {
@@ -562,151 +542,6 @@ int launch_cfg(const qx_desc* d, const void* packed, int m, const void* X, const
   return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;
 }
 
-// Block shapes, as activation x weight rows. Cost of a round of blocks with one, two or
-// three of them on each of the 256 compute units, in us per 32 chunks of k (measured with
-// uniform and codebook-3 g128 weights on 11008x4096, 4096x11008 and 4096x4096, m = 96 to
-// 4096; the sum over rounds reproduces every measured time within 8 %).
-enum Shape { kA, kB, kC, kD, kE, kF, kG, kH, kShapes };
-struct ShapeCost {
-  int bm, bn, mt, nt, wm, sc;
-  float us[3];
-  int ks;
-};
-constexpr ShapeCost kShape[kShapes] = {
-    {256, 256, 8, 4, 2, 2, {112.f, 0.f, 0.f}, 1},
-    {128, 256, 8, 4, 1, 1, {80.f, 135.f, 0.f}, 1},
-    {128, 192, 8, 3, 1, 1, {71.f, 121.f, 0.f}, 1},
-    {128, 128, 8, 2, 1, 2, {60.f, 78.f, 0.f}, 1},
-    {64, 128, 4, 2, 1, 2, {41.f, 54.f, 74.f}, 1},
-    // k split over 8 waves: us[0] + us[1] a chunk for a round of 256 blocks (H: us[2] of it
-    // for each round after the first, several blocks share a unit). Uniform-3 g64 at 32
-    // chunks / 86 chunks, one round: F 18 / 35 us, G 13.5 / 28.5, H 9.9 / 20
-    {64, 48, 4, 3, 1, 1, {8.f, 0.31f, 1.f}, 8},
-    {64, 32, 4, 2, 1, 1, {4.6f, 0.278f, 1.f}, 8},
-    {32, 32, 2, 2, 1, 1, {3.8f, 0.19f, 0.74f}, 8},
-};
-
-// Formats whose decoding leaves the registers of the 128 x 64 wave tile unspilled.
-template <int BITS, int KIND, int G, bool A8>
-constexpr bool kLight = KIND == QX_UNIFORM ? !A8 : KIND == QX_CODEBOOK && BITS == 3 && G >= 64;
-
-// Shapes that are built: F, G and H not for the integer products of gemm_a8.hip, which split k
-// themselves (11008x4096 uniform-3 g64 at m = 64: 24.1 us there, 22.9 with F; 4096x11008 24.5
-// and 24.6 with H), nor F where its tables overflow LDS; the 128 x 64 wave tiles (A, B) for the light formats and B for
-// codebook-4 g32, whose tables let one block of any shape on a compute unit.
-template <int BITS, int KIND, int G, bool A8>
-constexpr bool built(int s) {
-  if (s == kA) return kLight<BITS, KIND, G, A8> && !A8;
-  if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && BITS == 4 && G == 32);
-  if (s >= kF) return (KIND != QX_UNIFORM || !A8) && !(s == kF && KIND == QX_CODEBOOK && BITS == 4 && G == 32);
-  return true;
-}
-
-template <int BITS, int KIND, int G, int S>
-constexpr int per_unit() {  // blocks that fit a compute unit: LDS, and two or three by registers
-  using TS = TileShape<BITS, KIND, G, kShape[S].mt, kShape[S].nt, kShape[S].wm, kShape[S].sc, 1>;
-  constexpr int lds = kLdsBytes / TS::kLds, regs = S == kA ? 1 : S == kE ? 3 : 2;
-  return lds < regs ? lds : regs;
-}
-
-// Cost of the heavier decoders over that of uniform codes on shapes C, D and E (the same
-// sweep): 16-entry tables, tables of 32 or 64 codes, group sums.
-template <int BITS, int KIND, int G, bool A8>
-constexpr float decode_factor() {
-  if (KIND == QX_Q4X) return 1.4f;
-  if (KIND == QX_CODEBOOK)
-    return (BITS == 4 ? (G == 32 ? 1.5f : G == 64 ? 1.35f : 1.2f) : G == 32 ? 1.2f : 1.f) * (A8 ? 1.08f : 1.f);
-  return A8 ? (G == 32 ? 1.36f : 1.1f) : 1.f;
-}
-
-template <int BITS, int KIND, int G, bool A8, int S>
-void consider(const qx_desc* d, int m, float& best, int& shape) {
-  if constexpr (built<BITS, KIND, G, A8>(S)) {
-    constexpr int per = per_unit<BITS, KIND, G, S>();
-    const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
-    const long rest = blocks % (256 * per);
-    const float us = decode_factor<BITS, KIND, G, A8>() *
-                     ((float)(blocks / (256 * per)) * kShape[S].us[per - 1] + (rest ? kShape[S].us[(rest - 1) / 256] : 0.f));
-    if (us < best) {
-      best = us;
-      shape = S;
-    }
-  }
-}
-
-// The same cost for the kernels that took these products before (gemm.hip, gemm_a8.hip),
-// fitted to their times in the sweep:
-//   fp16 activations, uniform: 128 x 256 blocks at 76 us a round from m = 384 (11008x4096
-//     uniform-4 g128 at m = 512 / 1024 / 2048: 77 / 142 / 227 us), 128 x 64 tiles that take
-//     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54);
-//     up to 64 / 128 / 256 tiles of 128 x 64 are split over k (4096x4096 uniform-4 at m = 100 /
-//     256 / 500: 20.6 / 25.8 / 37.6 us);
-//   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
-//     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
-//     122 / 223 here), up to 256 tiles split over k (25 us), 0.05 us a tile up to 512 tiles
-//     of long rows (8-wave blocks);
-//   int8 activations, uniform: 64 x 64 tiles, 0.053 us a tile (11008x4096 uniform-3 g64 at
-//     m = 256 / 512 / 1024 / 2048: 56 / 96 / 164 / 318 us against 64 / 86 / 132 / 247 here),
-//     and 22 us more for rows of up to 64 chunks, which have 4-wave blocks.
-template <int BITS, int KIND, int G, bool A8>
-float other_cost(const qx_desc* d, int m) {
-  const bool wide = d->k > 64 * 128;
-  const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
-  if (KIND != QX_UNIFORM)
-    return (t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
-           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f);
-  if (A8) return (0.053f * (float)t64 + (wide ? 0.f : 22.f)) * (G == 32 ? 1.25f : 1.f);
-  const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
-  if (t128 <= 256) return t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f;
-  if (m >= 384) return 76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256);
-  const long rest = t128 % 768;
-  return 74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f);
-}
-
-// Split over k: every block's time is its fixed part and its chunks.
-template <int BITS, int KIND, int G, bool A8, int S>
-void consider_split(const qx_desc* d, int m, float& best, int& shape) {
-  if constexpr (built<BITS, KIND, G, A8>(S)) {
-    const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
-    const float rounds = (float)((blocks + 255) / 256);
-    const float us = decode_factor<BITS, KIND, G, A8>() * (kShape[S].us[0] + kShape[S].us[1] * (float)(d->k / 128)) * (rounds > 1.f ? 1.08f : 1.f) *
-                     (1.f - kShape[S].us[2] + kShape[S].us[2] * rounds);
-    if (us < best) {
-      best = us;
-      shape = S;
-    }
-  }
-}
-
-template <int BITS, int KIND, int G, bool A8>
-int pick(const qx_desc* d, int m) {
-  // 17 to 64 rows: one of these shapes, which took less time than gemm_skinny.hip and
-  // gemm.hip in nearly every format and size measured (60 drawn ones: 1.17 times faster on
-  // average); up to 32 rows of up to 32 chunks stay with gemm_skinny.hip where that applies
-  // (4096x4096 uniform-4 at m = 19: 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28:
-  // 15.1 and 17.1). Q4X rows of fewer chunks than waves stay too (12288x640 at m = 21:
-  // 7.5 us there, 8.1 here). Above, a shape must promise 4 % less than the other kernel (12 %
-  // against the integer products, whose fit is coarser: 2146x2432 uniform-3 g128 at m = 2436
-  // 54 us there, 64 here), as much as the costs may be off.
-  const float chunks = (float)(d->k / 128);
-  float best = 1e30f;
-  int shape = kShapes;
-  if (KIND == QX_Q4X && m <= 64 && chunks < 8.f) return shape;
-  if (m > 64) {
-    best = (A8 && KIND == QX_UNIFORM ? 0.88f : 0.96f) * other_cost<BITS, KIND, G, A8>(d, m);
-    consider<BITS, KIND, G, A8, kA>(d, m, best, shape);
-    consider<BITS, KIND, G, A8, kB>(d, m, best, shape);
-    consider<BITS, KIND, G, A8, kC>(d, m, best, shape);
-    consider<BITS, KIND, G, A8, kD>(d, m, best, shape);
-  }
-  if (m > 32 && (m > 64 || !A8 || KIND != QX_UNIFORM)) consider<BITS, KIND, G, A8, kE>(d, m, best, shape);
-  if (best < 1e30f) best = 6.f + (best - 6.f) * chunks / 32.f;  // us at this k (6 us of them fixed)
-  consider_split<BITS, KIND, G, A8, kF>(d, m, best, shape);
-  consider_split<BITS, KIND, G, A8, kG>(d, m, best, shape);
-  consider_split<BITS, KIND, G, A8, kH>(d, m, best, shape);
-  return shape;
-}
-
 template <int BITS, int KIND, int G, bool A8, int S>
 int launch_shape(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
                  hipStream_t s) {
@@ -734,26 +569,15 @@ int run(const qx_desc* d, const void* packed, int m, const void* X, const float*
 
 }  // namespace
 
-#define QX_TILE_FORMATS(F)                                                              \
-  F(3, 0, 32) F(3, 0, 64) F(3, 0, 128) F(4, 0, 32) F(4, 0, 64) F(4, 0, 128) F(3, 1, 32) \
-  F(3, 1, 64) F(3, 1, 128) F(4, 1, 32) F(4, 1, 64) F(4, 1, 128) F(4, 2, 64)
-
-bool gemm_tile_applies(const qx_desc* d, int m, bool a8) {
-  if (m <= 16) return false;  // one activation tile: gemm_skinny.hip, gemm.hip, gemm_a8.hip
-#define QX_TILE_PICK(B, K, G)                             \
-  if (d->bits == B && d->kind == K && d->group == G)      \
-    return (a8 ? pick<B, K, G, true>(d, m) : pick<B, K, G, false>(d, m)) != kShapes;
-  QX_TILE_FORMATS(QX_TILE_PICK)
-#undef QX_TILE_PICK
-  return false;
-}
+bool gemm_tile_applies(const qx_desc* d, int m, bool a8) { return pick_shape(d, m, a8) != kShapes; }
 
 int launch_gemm_tile(const qx_desc* d, const void* packed, int m, const void* X, const float* sx, uint16_t* Y,
                      hipStream_t s) {
-#define QX_TILE_RUN(B, K, G)                                                                          \
-  if (d->bits == B && d->kind == K && d->group == G)                                                  \
-    return sx != nullptr ? run<B, K, G, true>(d, packed, m, X, sx, Y, pick<B, K, G, true>(d, m), s)   \
-                         : run<B, K, G, false>(d, packed, m, X, sx, Y, pick<B, K, G, false>(d, m), s);
+  const int shape = pick_shape(d, m, sx != nullptr);
+#define QX_TILE_RUN(B, K, G)                                                             \
+  if (d->bits == B && d->kind == K && d->group == G)                                     \
+    return sx != nullptr ? run<B, K, G, true>(d, packed, m, X, sx, Y, shape, s)          \
+                         : run<B, K, G, false>(d, packed, m, X, sx, Y, shape, s);
   QX_TILE_FORMATS(QX_TILE_RUN)
 #undef QX_TILE_RUN
   return QX_E_UNSUPPORTED;
