@@ -137,13 +137,11 @@ __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
     const char* __restrict__ packed, const void* __restrict__ Xv, const float* __restrict__ sx,
     uint16_t* __restrict__ Y, int n, int k, int m, int nx, int my, int vec) {
   using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>;
-  constexpr int NTH = KS > 1 ? 64 : TS::kThreads, BM = TS::BM, BN = TS::BN, NG = TS::NG;
+  using TR = TileReads<BITS, KIND, G, MT, NT, WM, SC, KS, A8>;
+  constexpr int NTH = TR::NTH, BM = TS::BM, BN = TS::BN, NG = TS::NG, kXB = TR::kXB, kMRow = TR::kMRow;
   constexpr bool kSums = A8 && KIND != QX_CODEBOOK;  // group sums scaled in fp32
-  constexpr int XP = BM * 8 / NTH;                   // 16-byte activation pieces per thread and round
-  constexpr int CT = BITS * BN * SC, CP = (CT + NTH - 1) / NTH;
-  constexpr int MTOT = (KIND == QX_CODEBOOK ? TS::kMPlanes : 1) * BN * SC;  // table pieces, or rows x chunks
-  constexpr int MP = (MTOT + NTH - 1) / NTH;
-  constexpr int MD = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 2 : 4;  // dwords of one
+  constexpr int XP = TR::XP, CT = TR::CT, CP = TR::CP, MTOT = TR::MTOT, MP = TR::MP;
+  constexpr int MD = KIND == QX_UNIFORM ? NG : KIND == QX_Q4X ? 2 : 4;  // dwords of a table piece
   static_assert(BM * 8 % NTH == 0, "activation pieces divide evenly");
   __shared__ __align__(16) char lds[TS::kLds];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -175,29 +173,31 @@ __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
   // the clamped copies are never stored to Y or never multiplied) and their LDS writes.
   u32x4 xr[XP], cr[CP];
   uint32_t mr[MP][MD];
-  // Buffer loads: one 32-bit offset a thread and piece, the chunk in a scalar register, rows
-  // past the matrix outside the bounds (they read 0). The 64-bit addresses that the compiler
-  // keeps for plain loads would not leave room for the accumulators.
-  constexpr int kXB = A8 ? 1 : 2;  // bytes of an activation
-  constexpr int kMRow = KIND == QX_UNIFORM ? 4 : KIND == QX_Q4X ? 2 : TS::kTable;  // bytes of a group's word, scale or table
+  // Buffer loads: 32-bit offsets, rows past the matrix outside the bounds (they read 0). The
+  // 64-bit addresses that the compiler keeps for plain loads would not leave room for the
+  // accumulators.
   const int xrows = min(BM, m - m0), wrows = min(BN, n - n0);
-  const BufferRsrc xres = buffer(static_cast<const char*>(Xv) + (size_t)m0 * k * kXB, xrows * k * kXB);
+  BufferRsrc xres[XP];
+#pragma unroll
+  for (int i = 0; i < XP; ++i) {
+    const int row = TR::x_row(i, xrows);
+    xres[i] = buffer(static_cast<const char*>(Xv) + (size_t)(m0 + row) * k * kXB, (xrows - row) * k * kXB);
+  }
   const BufferRsrc cres = buffer(packed + (size_t)n0 * BITS * C * 16, wrows * BITS * C * 16);
   const BufferRsrc mres = buffer(packed + meta_off + (size_t)n0 * G_row * kMRow, wrows * G_row * kMRow);
   const int sel_words = (G_row + 15) / 16;
   const BufferRsrc sres = buffer(packed + meta_off + meta_off / 16 + (size_t)n0 * sel_words * 4,
                                  KIND == QX_Q4X ? wrows * sel_words * 4 : 0);
-  const int xoff = (t >> 3) * k * kXB + (t & 7) * 8 * kXB;
   auto load_x = [&](int c, int h) {
-    const int so = (min(c * KS + ks, C - 1) * 128 + h * 64) * kXB;
+    const int cx = min(c * KS + ks, C - 1);
+    const ReadAt r = TR::x(t, cx, h, k);
 #pragma unroll
     for (int i = 0; i < XP; ++i) {
-      const int so_i = so + i * (NTH / 8) * k * kXB;  // uniform
       if constexpr (A8) {
-        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(xres, xoff, so_i, 0));
+        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(xres[i], r.lane, r.scalar, 0));
         xr[i].x = v.x; xr[i].y = v.y;
       } else {
-        xr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, xoff, so_i, 0));
+        xr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xres[i], r.lane, r.scalar, 0));
       }
     }
   };
@@ -213,28 +213,6 @@ __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
       *reinterpret_cast<u32x4*>(xs + (KS > 1 ? 0 : buf) * TS::kXBuf + (p >> 3) * kXRow + ((p ^ (p >> 4)) & 7) * 16) = x_piece<BITS>(lo, hh);
     }
   };
-  // Code piece p = t + i * NTH of a super-round (SC chunks): SC neighbouring lanes take a
-  // row's SC pieces of a slice, in an order that spreads 16 rows over the LDS banks.
-  int coff[CP], moff[MP];
-#pragma unroll
-  for (int i = 0; i < CP; ++i) {
-    const int p = t + i * NTH, q = p / SC;
-    const int row = q % BN, cc = (p % SC) ^ (SC == 2 ? (row >> 3) & 1 : 0);
-    if constexpr (BN * SC % NTH == 0)  // the slice is uniform and goes to the scalar offset
-      coff[i] = (row * BITS * C + cc) * 16;
-    else
-      coff[i] = ((row * BITS + min(q / BN, BITS - 1)) * C + cc) * 16;
-  }
-#pragma unroll
-  for (int i = 0; i < MP; ++i) {
-    const int p = min(t + i * NTH, MTOT - 1);
-    if constexpr (KIND == QX_CODEBOOK)  // a row's tables of the super-round are one run
-      moff[i] = p / (TS::kMPlanes * SC) * G_row * kMRow + p % (TS::kMPlanes * SC) * 16;
-    else if constexpr (KIND == QX_UNIFORM)
-      moff[i] = (p / SC * G_row + p % SC * NG) * 4;
-    else
-      moff[i] = p;
-  }
   // Codes and tables of super-round j. Past the last chunk of a row the loads run on into
   // what follows (or out of bounds, 0); it is never multiplied.
   static_assert(KS == 1 || SC == 1, "waves on their own chunks take them one by one");
@@ -242,30 +220,26 @@ __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
   auto load_codes = [&](int j) {
     const int c = KS > 1 ? min(j * KS + ks, C - 1) : min(j, last_j) * SC;
 #pragma unroll
-    for (int i = 0; i < CP; ++i)
-      cr[i] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                     cres, coff[i], (BN * SC % NTH == 0 ? (i * NTH / (BN * SC)) * C + c : c) * 16, 0));
+    for (int i = 0; i < CP; ++i) {
+      const ReadAt r = TR::code(t, i, c, C);
+      cr[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(cres, r.lane, r.scalar, 0));
+    }
 #pragma unroll
     for (int i = 0; i < MP; ++i) {
-      if constexpr (KIND == QX_CODEBOOK) {
-        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(mres, moff[i], c * NG * kMRow, 0));
+      const ReadAt r = TR::meta(t, i, c, G_row);
+      if constexpr (KIND == QX_Q4X) {  // the scales of a chunk's groups and their selectors (4 bits)
+        const ReadAt w = TR::selectors(t, i, c, sel_words);
+        mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, r.lane, r.scalar, 0);
+        mr[i][1] = __builtin_amdgcn_raw_buffer_load_b32(sres, w.lane, w.scalar, 0) >>
+                   (4 * ((c + TR::meta_piece(t, i) % SC) % 8));
+      } else if constexpr (TR::kMBytes == 4) {
+        mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, r.lane, r.scalar, 0);
+      } else if constexpr (TR::kMBytes == 8) {
+        const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(mres, r.lane, r.scalar, 0));
+        mr[i][0] = v.x; mr[i][1] = v.y;
+      } else {
+        const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(mres, r.lane, r.scalar, 0));
         mr[i][0] = v.x; mr[i][1] = v.y; mr[i][2] = v.z; mr[i][3] = v.w;
-      } else if constexpr (KIND == QX_UNIFORM) {
-        const int so = c * NG * 4;
-        if constexpr (NG == 1) {
-          mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, moff[i], so, 0);
-        } else if constexpr (NG == 2) {
-          const u32x2 v = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(mres, moff[i], so, 0));
-          mr[i][0] = v.x; mr[i][1] = v.y;
-        } else {
-          const u32x4 v = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(mres, moff[i], so, 0));
-          mr[i][0] = v.x; mr[i][1] = v.y; mr[i][2] = v.z; mr[i][3] = v.w;
-        }
-      } else {  // the scales of a chunk's groups and their selectors (4 bits)
-        const int row = moff[i] / SC, cm = c + moff[i] % SC;
-        mr[i][0] = __builtin_amdgcn_raw_buffer_load_b32(mres, row * G_row * 2 + moff[i] % SC * 4, 4 * c, 0);
-        mr[i][1] = __builtin_amdgcn_raw_buffer_load_b32(sres, (row * sel_words + cm / 8) * 4, 0, 0) >> (4 * (cm % 8));
       }
     }
   };

@@ -28,6 +28,64 @@ struct TileShape {
   static constexpr int kWaves = KS > 1 ? KS / 4 * (2 * kLds <= kLdsBytes ? 2 : 1) : WM == 2 || 2 * kLds <= kLdsBytes ? 2 : 1;
 };
 
+// Where a lane's load reads, in bytes from its buffer's start: `lane`, which is held against
+// the buffer's size (a load past it reads 0), and `scalar`, which the compiler defines as
+// outside that check and the hardware as taken from the size. All that can leave the buffer is
+// therefore in `lane` or in the buffer itself: rows past the matrix, and with SC = 2 the chunk,
+// since a super-round can begin in the last one. `scalar` stays within a row.
+struct ReadAt {
+  int lane, scalar;
+};
+
+// The loads of thread t of NTH that stage half h of chunk c's activations, and piece i of the
+// codes and group constants of the super-round that begins with chunk c.
+template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, int KS, bool A8>
+struct TileReads {
+  using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>;
+  static constexpr int NTH = KS > 1 ? 64 : TS::kThreads, BN = TS::BN, NG = TS::NG;
+  static constexpr int kXB = A8 ? 1 : 2;  // bytes of an activation
+  static constexpr int kMRow = KIND == QX_UNIFORM ? 4 : KIND == QX_Q4X ? 2 : TS::kTable;  // of a group's word, scale or table
+  static constexpr int XP = TS::BM * 8 / NTH;  // 16-byte activation pieces per thread and round
+  static constexpr int CT = BITS * BN * SC, CP = (CT + NTH - 1) / NTH;
+  static constexpr int MTOT = (KIND == QX_CODEBOOK ? TS::kMPlanes : 1) * BN * SC;  // table pieces, or rows x chunks
+  static constexpr int MP = (MTOT + NTH - 1) / NTH;
+  static constexpr int kXBytes = 8 * kXB, kCBytes = 16;  // of one load
+  static constexpr int kMBytes = KIND == QX_UNIFORM ? 4 * NG : KIND == QX_Q4X ? 4 : 16;
+
+  __host__ __device__ static ReadAt at(int lane, int scalar) {
+    return SC == 1 ? ReadAt{lane, scalar} : ReadAt{lane + scalar, 0};
+  }
+  // Piece i of all threads has a buffer of its own, from its first row to the tile's last of
+  // `rows` (a piece past them: the last row alone). With one buffer and the piece's row in
+  // `lane` the additions cost 1.5 % (22016x4096 and 4096x11008 uniform-4 with 12288x4096 and
+  // 4096x4096 codebook-3 at m = 2048: 903 against 887 us).
+  __host__ __device__ static int x_row(int i, int rows) { return i * (NTH / 8) < rows ? i * (NTH / 8) : rows - 1; }
+  __host__ __device__ static ReadAt x(int t, int c, int h, int k) {
+    return {(t >> 3) * k * kXB + (t & 7) * 8 * kXB, (c * 128 + h * 64) * kXB};
+  }
+  // Code piece p of a super-round: SC neighbouring lanes take a row's SC pieces of a slice, in
+  // an order that spreads 16 rows over the LDS banks.
+  __host__ __device__ static ReadAt code(int t, int i, int c, int C) {
+    const int p = t + i * NTH, q = p / SC, row = q % BN, cc = (p % SC) ^ (SC == 2 ? (row >> 3) & 1 : 0);
+    if (BN * SC % NTH == 0)  // the slice is uniform
+      return at((row * BITS * C + cc) * 16, (i * NTH / (BN * SC) * C + c) * 16);
+    const int slice = q / BN < BITS ? q / BN : BITS - 1;
+    return at(((row * BITS + slice) * C + cc) * 16, c * 16);
+  }
+  __host__ __device__ static int meta_piece(int t, int i) { return t + i * NTH < MTOT ? t + i * NTH : MTOT - 1; }
+  __host__ __device__ static ReadAt meta(int t, int i, int c, int G_row) {
+    const int p = meta_piece(t, i);
+    if (KIND == QX_CODEBOOK)  // a row's tables of the super-round are one run
+      return at(p / (TS::kMPlanes * SC) * G_row * kMRow + p % (TS::kMPlanes * SC) * 16, c * NG * kMRow);
+    return at((p / SC * G_row + p % SC * NG) * kMRow, c * NG * kMRow);
+  }
+  // Q4X: the word with the selectors of the piece's chunk
+  __host__ __device__ static ReadAt selectors(int t, int i, int c, int sel_words) {
+    const int p = meta_piece(t, i);
+    return {(p / SC * sel_words + (c + p % SC) / 8) * 4, 0};
+  }
+};
+
 // Block shapes, as activation x weight rows. Cost of a round of blocks with one, two or
 // three of them on each of the 256 compute units, in us per 32 chunks of k (measured with
 // uniform and codebook-3 g128 weights on 11008x4096, 4096x11008 and 4096x4096, m = 96 to

@@ -1,19 +1,20 @@
-// The host side of gemm_tile.hip for the CPU tests (compiled for the host alone; no kernel is
-// launched). Arguments:
+// The host side of the tiled GEMM for the CPU tests. Arguments:
 //   reads  checks where the loads of every built kernel read: every thread, piece and chunk, for
 //          1 .. BM activation rows and 1 .. BN weight rows in a block; prints one line per kernel
 //          with the number of loads that leave their buffer by either rule of the range check
-//   pick   reads "bits kind group a8 n k m" from standard input, prints the picked shape's index
+//   pick   reads "bits kind group a8 n k m" from standard input, prints the shape's letter, or -
 #include <cstdio>
 #include <cstring>
 
-#include "../../paper_2505_07531_amd/csrc/gemm_tile.hip"
+#include "../../paper_2505_07531_amd/csrc/gemm_tile_plan.h"
 
-namespace qx {
+using namespace qx;
+using namespace qx::tile;
+
 namespace {
 
-// The load passes the check (or part of it does) by one of two rules, the scalar offset left out
-// of it or taken from the size, and its bytes are not all in the buffer.
+// The load passes the range check by one of two rules (the scalar offset left out of it, or taken
+// from the size) and its bytes are not all in the buffer.
 bool leaves(ReadAt r, int size, int bytes) {
   const bool out = (unsigned)r.lane >= (unsigned)size;
   const bool out_sub = (unsigned)r.lane >= (unsigned)size - (unsigned)r.scalar;
@@ -30,10 +31,13 @@ void check_reads() {
       const int k = 128 * C, G_row = k / G, words = (G_row + 15) / 16;
       for (int t = 0; t < TR::NTH; ++t) {
         for (int rows = 1; rows <= sh.bm; ++rows)
-          for (int i = 0; i < TR::XP; ++i)
+          for (int i = 0; i < TR::XP; ++i) {
+            const int row = TR::x_row(i, rows), first = i * (TR::NTH / 8);
+            bad_x += row < 0 || row >= rows || (first < rows && row != first);
             for (const int h : {0, 1})
               for (int c = 0; c < C; c += C > 1 ? C - 1 : 1)
-                bad_x += leaves(TR::x(TR::x_first(t, k), i, c, h, k), rows * k * TR::kXB, TR::kXBytes);
+                bad_x += leaves(TR::x(t, c, h, k), (rows - row) * k * TR::kXB, TR::kXBytes);
+          }
         for (int rows = 1; rows <= sh.bn; ++rows)
           for (int c = 0; c < C; c += sh.sc) {
             for (int i = 0; i < TR::CP; ++i) bad_code += leaves(TR::code(t, i, c, C), rows * BITS * C * 16, TR::kCBytes);
@@ -48,23 +52,17 @@ void check_reads() {
   }
 }
 
-template <int BITS, int KIND, int G, bool A8>
+template <int BITS, int KIND, int G, bool A8, int S = 0>
 void check_format() {
-  check_reads<BITS, KIND, G, A8, kA>();
-  check_reads<BITS, KIND, G, A8, kB>();
-  check_reads<BITS, KIND, G, A8, kC>();
-  check_reads<BITS, KIND, G, A8, kD>();
-  check_reads<BITS, KIND, G, A8, kE>();
-  check_reads<BITS, KIND, G, A8, kF>();
-  check_reads<BITS, KIND, G, A8, kG>();
-  check_reads<BITS, KIND, G, A8, kH>();
+  if constexpr (S < kShapes) {
+    check_reads<BITS, KIND, G, A8, S>();
+    check_format<BITS, KIND, G, A8, S + 1>();
+  }
 }
 
 }  // namespace
-}  // namespace qx
 
 int main(int argc, char** argv) {
-  using namespace qx;
   if (argc == 2 && std::strcmp(argv[1], "reads") == 0) {
 #define CHECK(B, K, G) check_format<B, K, G, false>(), check_format<B, K, G, true>();
     QX_TILE_FORMATS(CHECK)
@@ -74,11 +72,8 @@ int main(int argc, char** argv) {
     int b, kd, g, a8, n, k, m;
     while (std::scanf("%d %d %d %d %d %d %d", &b, &kd, &g, &a8, &n, &k, &m) == 7) {
       const qx_desc d = {n, k, b, g, kd, 0};
-      int shape = kShapes;
-#define PICK(B, K, G) \
-  if (b == B && kd == K && g == G && m > 16) shape = a8 ? pick<B, K, G, true>(&d, m) : pick<B, K, G, false>(&d, m);
-      QX_TILE_FORMATS(PICK)
-      std::printf("%d\n", shape == kShapes ? -1 : shape);
+      const int shape = pick_shape(&d, m, a8 != 0);
+      std::printf("%c\n", shape == kShapes ? '-' : 'A' + shape);
     }
     return 0;
   }
