@@ -22,6 +22,10 @@ int launch_gemm_lut_a8(const qx_desc*, const void*, int, const int8_t*, const fl
 int launch_gemv_a8q(const qx_desc*, const void*, const int8_t*, const float*, uint16_t*, hipStream_t) {
   return QX_E_HIP;
 }
+bool gemm_tile_applies(const qx_desc*, int, bool) { return false; }
+int launch_gemm_tile(const qx_desc*, const void*, int, const void*, const float*, uint16_t*, hipStream_t) {
+  return QX_E_HIP;
+}
 bool gemv_multi_applies(const qx_desc*, int) { return false; }
 int launch_gemv_multi(const qx_desc*, const void*, int, const uint16_t*, uint16_t*, hipStream_t) {
   return QX_E_HIP;

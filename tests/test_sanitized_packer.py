@@ -52,12 +52,17 @@ def _build(tmp, flags, name):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("g++ not available")
+    probe = os.path.join(tmp, "probe.cpp")
+    with open(probe, "w") as f:
+        f.write("int main() { return 0; }\n")
+    r = subprocess.run([gxx, *flags, probe, "-o", os.path.join(tmp, "probe"), "-pthread"], capture_output=True, text=True)
+    if r.returncode != 0:  # the sanitizer itself is missing
+        pytest.skip(f"sanitizer unavailable: {r.stderr[-400:]}")
     exe = os.path.join(tmp, name)
     cmd = [gxx, "-O1", "-g", "-std=c++17", *flags, "-fno-omit-frame-pointer", "-D__HIP_PLATFORM_AMD__",
            "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), *SRC, "-o", exe, "-pthread"]
     r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        pytest.skip(f"sanitized build unavailable: {r.stderr[-400:]}")
+    assert r.returncode == 0, r.stderr[-2000:]  # a launcher without a stand-in, say
     return exe
 
 
