@@ -505,9 +505,8 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
       break;
     }
     case 2:
-      // 17 to 64 rows: Q4X rows of few chunks (everything else takes gemm_tile.hip there)
-      if constexpr (KIND == QX_Q4X) launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, 2, A8>(d, p, m, X, sx, Y, s);
-      else return QX_E_UNSUPPORTED;
+      // 17 to 64 rows: several rounds of tiles, or short rows (small_tiles_win in gemm_tile_plan.h)
+      launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, kUni ? 1 : 2, A8>(d, p, m, X, sx, Y, s);
       break;
     default:
       if constexpr (kUni) {

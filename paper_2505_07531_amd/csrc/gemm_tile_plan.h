@@ -202,20 +202,62 @@ void consider_split(const qx_desc* d, int m, float& best, int& shape) {
   }
 }
 
+// 17 to 64 rows: whether the 32 x 32 tiles of gemm.hip (4 waves, k over two of them) take less
+// time than every shape here. They have a shorter start and end than a k split over 8 waves,
+// which counts where rows are short, and hold three and more tiles on a compute unit, which
+// streams the codes and tables faster where there are several rounds of tiles and decoding is
+// heavy. Measured in all formats, n = 4096 to 28672, k = 1024 to 11008, m = 24 and 48 (us there
+// and in the best shape here; up to 32 rows unless stated):
+//   more than 512 weight tiles: 22016x5120 codebook-4 g32 54.6 / 71.7, 22016x8192 codebook-4 g64
+//     61.5 / 76.2, 22016x2048 codebook-4 g128 16.5 / 18.6, uniform-4 g128 14.3 / 16.5, Q4X
+//     18.0 / 20.4, 22016x8192 codebook-3 g32 57.8 / 65.5; the lighter decoders only where rows
+//     are short: 22016 rows uniform-3 g64 at 8 / 16 / 32 chunks 10.0 / 11.8, 16.1 / 16.8, 27.3 / 25.3;
+//   257 to 512: codebook-4 g32 always (11008x4096 26.4 / 31.2), codebook-4 g64 and Q4X up to 40
+//     chunks (11008x2048 13.8 / 16.2, 11008x4096 Q4X 21.4 / 22.9; 11008x8192 41.5 / 37.6 and
+//     38.6 / 38.7), others up to 16 or 12; uniform-4 up to 384 tiles, where the shapes here have
+//     one round of 64 x 48 for half as many rows, up to 40 (12288x5120 g128 21.6 / 23.5; beyond,
+//     14336x5120 g32 24.1 / 23.0);
+//   33 to 64 rows: where 64 x 128 tiles leave half of the units idle (14336x1024 Q4X 12.7 / 16.7,
+//     uniform-4 g128 10.5 / 13.0, uniform-3 g64 12.0 / 12.6; 18944x2048 codebook-4 g64 25.4 /
+//     30.3), and codebook-4 g32, whose tables leave room for one of them (11008x4096 36.9 / 43.5);
+//     rows of up to 8 chunks in 193 or 257 to 384 weight tiles (8103x768 uniform-4 6.6 / 7.2,
+//     11008x1024 codebook-4 g128 9.7 / 10.4).
+// Q4X and codebook-4 g32 rows of few chunks: Q4X 12288x640 at m = 21 7.5 / 8.1, 4096x1024 at m = 24 5.9 / 6.3;
+// codebook-4 g32 639x640 at m = 27 5.8 / 6.1.
+template <int BITS, int KIND, int G, bool A8>
+bool small_tiles_win(const qx_desc* d, int m) {
+  constexpr int kAll = 1 << 20;  // chunks
+  constexpr bool kQ4x = KIND == QX_Q4X, kCb4g32 = KIND == QX_CODEBOOK && BITS == 4 && G == 32;
+  const int chunks = d->k / 128, tiles = (d->n + 31) / 32;
+  if (kQ4x && tiles <= (m <= 32 ? 256 : 512) && chunks <= (A8 ? 7 : 8)) return true;
+  if (kCb4g32 && !A8 && tiles <= 256 && chunks <= 8) return true;
+  if (m <= 32) {
+    if (tiles <= 256) return false;
+    const bool two = tiles <= 512;
+    if (kQ4x) return chunks <= (A8 ? (two ? 16 : 40) : two ? 40 : kAll);
+    if (KIND == QX_UNIFORM) return chunks <= (BITS == 3 ? (two ? 12 : 16) : !two ? kAll : tiles <= 384 ? 40 : 16);
+    if (BITS == 3) return chunks <= (G == 32 ? (A8 ? (two ? 12 : 16) : two ? 16 : kAll) : A8 ? 0 : 12);
+    if (G == 128) return chunks <= (A8 ? 0 : two ? 16 : kAll);
+    return chunks <= (G == 32 || !two ? kAll : A8 ? 16 : 40);
+  }
+  if (kCb4g32) return tiles > 256 && (tiles <= 384 ? chunks <= (A8 ? 64 : kAll) : tiles <= 512 ? chunks <= 8 : !A8 && tiles <= 600);
+  if (BITS == 4 && !A8 && tiles > (KIND == QX_UNIFORM ? 192 : 256) && tiles <= 384 && chunks <= 8) return true;
+  if (tiles <= 384 || tiles > (A8 || BITS == 3 ? 512 : kQ4x ? 700 : 600)) return false;
+  return chunks <= (BITS == 3 ? (A8 ? 0 : 8) : A8 && !kQ4x ? 8 : 16);
+}
+
 template <int BITS, int KIND, int G, bool A8>
 int pick(const qx_desc* d, int m) {
-  // 17 to 64 rows: one of these shapes, which took less time than gemm_skinny.hip and
-  // gemm.hip in nearly every format and size measured (60 drawn ones: 1.17 times faster on
-  // average); up to 32 rows of up to 32 chunks stay with gemm_skinny.hip where that applies
-  // (4096x4096 uniform-4 at m = 19: 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28:
-  // 15.1 and 17.1). Q4X rows of fewer chunks than waves stay too (12288x640 at m = 21:
-  // 7.5 us there, 8.1 here). Above, a shape must promise 4 % less than the other kernel (12 %
+  // 17 to 64 rows: one of these shapes unless small_tiles_win; qx_gemm keeps up to 32 rows of
+  // up to 32 chunks with gemm_skinny.hip where that applies (4096x4096 uniform-4 at m = 19:
+  // 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28: 15.1 and 17.1). Above, a shape
+  // must promise 4 % less than the other kernel (12 %
   // against the integer products, whose fit is coarser: 2146x2432 uniform-3 g128 at m = 2436
   // 54 us there, 64 here), as much as the costs may be off.
   const float chunks = (float)(d->k / 128);
   float best = 1e30f;
   int shape = kShapes;
-  if (KIND == QX_Q4X && m <= 64 && chunks < 8.f) return shape;
+  if (m <= 64 && (!A8 || KIND != QX_UNIFORM) && small_tiles_win<BITS, KIND, G, A8>(d, m)) return shape;
   if (m > 64) {
     best = (A8 && KIND == QX_UNIFORM ? 0.88f : 0.96f) * other_cost<BITS, KIND, G, A8>(d, m);
     consider<BITS, KIND, G, A8, kA>(d, m, best, shape);

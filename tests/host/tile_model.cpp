@@ -2,11 +2,51 @@
 //   reads  checks where the loads of every built kernel read: every thread, piece and chunk, for
 //          1 .. BM activation rows and 1 .. BN weight rows in a block; prints one line per kernel
 //          with the number of loads that leave their buffer by either rule of the range check
-//   pick   reads "bits kind group a8 n k m" from standard input, prints the shape's letter, or -
+//   route  reads "bits kind group a8 n k m" from standard input (more than 4 rows) and prints the
+//          kernel that qx_gemm or qx_gemm_a8 launches: the letter of a tiled shape, or its file
 #include <cstdio>
 #include <cstring>
 
+#include "../../paper_2505_07531_amd/csrc/gemm_skinny_plan.h"
 #include "../../paper_2505_07531_amd/csrc/gemm_tile_plan.h"
+
+// Stand-ins for the launchers that qx_api.cpp calls.
+static char g_route[16];
+static int took(const char* name) {
+  std::snprintf(g_route, sizeof g_route, "%s", name);
+  return QX_OK;
+}
+namespace qx {
+int launch_dequant(const qx_desc*, const void*, int, void*, hipStream_t) { return QX_E_HIP; }
+int launch_gemv(const qx_desc*, const void*, const uint16_t*, uint16_t*, hipStream_t) { return QX_E_HIP; }
+int launch_gemv_a8(const qx_desc*, const void*, const uint16_t*, uint16_t*, hipStream_t) { return QX_E_HIP; }
+int launch_quantize_a8(int, int, const uint16_t*, int8_t*, float*, hipStream_t) { return QX_E_HIP; }
+int launch_gemv_a8_multi(const qx_desc*, const void*, int, const int8_t*, const float*, uint16_t*, hipStream_t) {
+  return QX_E_HIP;
+}
+int launch_gemv_lut_a8(const qx_desc*, const void*, const uint16_t*, uint16_t*, hipStream_t) { return QX_E_HIP; }
+int launch_gemv_a8q(const qx_desc*, const void*, const int8_t*, const float*, uint16_t*, hipStream_t) {
+  return QX_E_HIP;
+}
+bool gemv_multi_applies(const qx_desc*, int) { return false; }
+int launch_gemv_multi(const qx_desc*, const void*, int, const uint16_t*, uint16_t*, hipStream_t) { return QX_E_HIP; }
+int launch_gemm(const qx_desc*, const void*, int, const uint16_t*, uint16_t*, hipStream_t) { return took("gemm"); }
+int launch_gemm_a8(const qx_desc*, const void*, int, const int8_t*, const float*, uint16_t*, hipStream_t) {
+  return took("gemm_a8");
+}
+int launch_gemm_lut_a8(const qx_desc*, const void*, int, const int8_t*, const float*, uint16_t*, hipStream_t) {
+  return took("gemm");
+}
+bool gemm_skinny_applies(const qx_desc* d, int m) { return skinny_applies(d, m); }
+int launch_gemm_skinny(const qx_desc*, const void*, int, const uint16_t*, uint16_t*, hipStream_t) {
+  return took("skinny");
+}
+bool gemm_tile_applies(const qx_desc* d, int m, bool a8) { return tile::pick_shape(d, m, a8) != tile::kShapes; }
+int launch_gemm_tile(const qx_desc* d, const void*, int m, const void*, const float* sx, uint16_t*, hipStream_t) {
+  const char name[2] = {(char)('A' + tile::pick_shape(d, m, sx != nullptr)), 0};
+  return took(name);
+}
+}  // namespace qx
 
 using namespace qx;
 using namespace qx::tile;
@@ -68,12 +108,15 @@ int main(int argc, char** argv) {
     QX_TILE_FORMATS(CHECK)
     return 0;
   }
-  if (argc == 2 && std::strcmp(argv[1], "pick") == 0) {
+  if (argc == 2 && std::strcmp(argv[1], "route") == 0) {
+    alignas(16) static char buf[16];  // pointers that pass the checks; nothing is read or written
+    uint16_t* const h = reinterpret_cast<uint16_t*>(buf);
     int b, kd, g, a8, n, k, m;
     while (std::scanf("%d %d %d %d %d %d %d", &b, &kd, &g, &a8, &n, &k, &m) == 7) {
       const qx_desc d = {n, k, b, g, kd, 0};
-      const int shape = pick_shape(&d, m, a8 != 0);
-      std::printf("%c\n", shape == kShapes ? '-' : 'A' + shape);
+      const int st = a8 ? qx_gemm_a8(&d, buf, m, reinterpret_cast<int8_t*>(buf), reinterpret_cast<float*>(buf), h, nullptr)
+                        : qx_gemm(&d, buf, m, h, h, nullptr);
+      std::printf("%s\n", st == QX_OK ? g_route : "error");
     }
     return 0;
   }

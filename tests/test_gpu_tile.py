@@ -20,7 +20,9 @@ FORMATS = [(*f, g) for f in (U3, U4, C3, C4) for g in (32, 64, 128)] + [(4, 2, 6
 # and numbers that leave some waves one chunk short.
 SIZES = [(500, 128, 70), (1376, 1024, 77), (4001, 1408, 40), (1001, 1152, 17), (333, 11008, 65), (4096, 11008, 100),
          (11008, 256, 64), (4099, 128, 500), (11009, 384, 258), (11008, 256, 521), (5506, 640, 1025), (22013, 256, 1030),
-         (4096, 128, 2048)]
+         (4096, 128, 2048),
+         # 17 to 64 rows in the 32 x 32 tiles of gemm.hip (fp16): an odd number of chunks, one and two tiles
+         (12305, 640, 21), (12309, 1024, 50)]
 
 
 def quant(fmt, n, k):

@@ -1,5 +1,5 @@
 """The host side of the tiled GEMM (gemm_tile_plan.h), compiled with g++: where its kernels'
-loads read. CPU only."""
+loads read, and which products qx_gemm and qx_gemm_a8 give to it. CPU only."""
 import os
 import shutil
 import subprocess
@@ -18,7 +18,7 @@ def tile_model(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("tile") / "tile_model")
     subprocess.run([gxx, "-O2", "-std=c++17", "-Wno-unused-function", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
                     "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host", "tile_model.cpp"),
-                    "-o", exe], check=True)
+                    os.path.join(ROOT, "paper_2505_07531_amd", "csrc", "qx_api.cpp"), "-o", exe, "-pthread"], check=True)
 
     def run(what, text=""):
         return subprocess.run([exe, what], input=text, capture_output=True, text=True, check=True,
@@ -34,3 +34,37 @@ def test_tile_loads_stay_in_their_buffers(tile_model):
     assert len(lines) > 100
     bad = [line for line in lines if line.split()[5:] != ["0", "0", "0"]]
     assert not bad, (len(bad), bad[:8])
+
+
+FORMATS = {f"{'uc'[kind]}{b}g{g}": (b, kind, g) for b in (3, 4) for kind in (0, 1) for g in (32, 64, 128)}
+FORMATS["q4x"] = (4, 2, 64)
+
+
+def routes(tile_model, cases):
+    """The kernel of each (format, int8 rows, n, k, m)."""
+    return tile_model("route", "".join("%d %d %d %d %d %d %d\n" % (*FORMATS[f], a8, n, k, m) for f, a8, n, k, m in cases))
+
+
+# (format, int8 rows, n, k, m): us in gemm.hip, us in the tiled shape that had taken the product
+SMALL_TILES = {
+    ("c4g32", 0, 11008, 4096, 24): (26.4, 31.2), ("c4g32", 0, 22016, 5120, 24): (54.6, 71.7),
+    ("c4g32", 0, 11008, 4096, 48): (36.9, 43.5), ("c4g32", 1, 11008, 4096, 48): (41.7, 45.5),
+    ("c4g64", 0, 22016, 8192, 24): (61.5, 76.2), ("c4g64", 1, 22016, 1024, 24): (13.9, 18.0),
+    ("c4g128", 0, 22016, 2048, 24): (16.5, 18.6), ("q4x", 0, 12288, 4096, 24): (21.9, 23.7),
+    ("c3g32", 0, 18944, 8192, 24): (53.0, 54.4), ("u4g128", 0, 12288, 5120, 24): (21.6, 23.5),
+    ("u4g32", 0, 22016, 2048, 24): (15.5, 17.5), ("u3g128", 0, 22016, 1024, 24): (9.5, 11.5),
+    ("q4x", 0, 14336, 1024, 48): (12.7, 16.7), ("u4g128", 0, 18944, 2048, 48): (19.8, 22.3),
+}
+
+
+def test_short_and_tall_products_of_few_rows(tile_model):
+    """17 to 64 rows, several rounds of blocks: the formats and chunk counts at which the
+    32 x 32 tiles of gemm.hip measured faster than the tiled shapes go there."""
+    got = dict(zip(SMALL_TILES, routes(tile_model, SMALL_TILES)))
+    assert all(r == "gemm" for r in got.values()), got
+    # and those that measured slower there stay: (33.7, 28.3), (16.6, 11.1), (47.8, 40.4) us
+    keep = [("c4g32", 0, 8192, 8192, 24), ("c3g128", 0, 4096, 5120, 24), ("c4g32", 0, 8192, 11008, 24)]
+    assert all(r in "EFGH" for r in routes(tile_model, keep))
+    # the sizes by which test_gpu_tile.py runs that kernel in every format
+    edges = [(f, 0, n, k, m) for f in FORMATS for n, k, m in ((12305, 640, 21), (12309, 1024, 50))]
+    assert set(routes(tile_model, edges)) == {"gemm"}
