@@ -1,5 +1,5 @@
 // Small-batch quantized GEMM on the matrix cores: Y[m][n] = sum_k X[m][k] W'[n][k]
-// for 2 <= m <= 32 activation rows (decode of several sequences, short prefill chunks).
+// for 2 <= m <= 48 activation rows (decode of several sequences, short prefill chunks).
 //
 // With few activation rows the product is still bound by streaming the packed
 // weights (decoding is memory-bound, Section 2.4 of the paper), so this kernel
@@ -546,9 +546,16 @@ int launch_cfg(const qx_desc* d, const char* p, int m, const uint16_t* X, uint16
   if (m <= 16)
     hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 1>), dim3(blocks), dim3(64 * W), lds, s, p, X,
                        Y, d->n, d->k, m, red_off);
-  else if constexpr (J == 1 && RF <= 3)  // two activation tiles: rows of at most 32 chunks
-    hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 2>), dim3(blocks), dim3(64 * W), lds, s, p, X,
-                       Y, d->n, d->k, m, red_off);
+  else if constexpr (J == 1 && RF <= 3) {  // two or three activation tiles: rows of at most 32 chunks
+    constexpr bool kThird = RF == 1 && third_tile(BITS, KIND, G);
+    if (m > 32 && !kThird) return QX_E_UNSUPPORTED;
+    if (m <= 32)
+      hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 2>), dim3(blocks), dim3(64 * W), lds, s, p, X,
+                         Y, d->n, d->k, m, red_off);
+    else if constexpr (kThird)  // its own form: three tiles for 17 to 32 rows took up to 3 % longer than two
+      hipLaunchKernelGGL((gemm_skinny_kernel<BITS, KIND, G, RF, J, LB, 3>), dim3(blocks), dim3(64 * W), lds, s, p, X,
+                         Y, d->n, d->k, m, red_off);
+  }
   else
     return QX_E_UNSUPPORTED;
   return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;

@@ -6,6 +6,11 @@
 
 namespace qx {
 
+// Formats with a form for a third activation tile (33 to 48 rows).
+constexpr bool third_tile(int bits, int kind, int group) {
+  return kind != QX_Q4X && !(kind == QX_CODEBOOK && group == 32) && !(kind == QX_CODEBOOK && bits == 4 && group == 64);
+}
+
 // Whether qx_gemm runs m rows on this kernel. Beyond 16 rows (a second activation tile,
 // every code decoded again for it) only up to 32 of at most 32 chunks with one round of
 // blocks (us at m = 24 / 32 against the matrix-core GEMM of gemm.hip, weights rotated over
@@ -13,7 +18,12 @@ namespace qx {
 // 15.0 / 15.8 vs 19.9 / 19.9; 4096x4096 codebook-3 8.9 / 9.1 vs 14.8 / 14.9; 22016 rows, two
 // rounds: 28.5 / 30.2 vs 24.5 / 24.9; against gemm_tile.hip 15.1 vs 17.1 at 12288x4096
 // codebook-3, m = 28, and 8.1 vs 9.6 at 4096x4096 uniform-4, m = 19, but 29.9 vs 18.4 at
-// 11008x4096 uniform-3 g64, m = 64). Up to 16 rows: measured against the
+// 11008x4096 uniform-3 g64, m = 64). A third tile only on matrices of up to 4096 rows and 29 to
+// 32 chunks (4096x4096 at m = 33 / 40 / 48 against gemm_tile.hip: codebook-4 g128 10.2 / 10.3 /
+// 10.9 vs 12.0 / 11.9 / 11.7, uniform-3 g64 9.2 / 9.5 / 10.1 vs 10.4 / 10.2 / 10.2, uniform-4
+// g128 9.5 / 9.8 / 10.3 vs 10.4 / 10.3 / 10.2, on 1376 rows 9.1 vs 8.9 at m = 40; codebook-3 g32
+// 12.0 vs 10.9 at m = 33; 4096x3712 codebook-3 g128 9.9 vs 9.2 at m = 48, 3072x3712 uniform-4
+// g128 9.0 vs 8.7 at m = 33). Up to 16 rows: measured against the
 // small-batch GEMV-style kernel (m <= 4) and the matrix-core GEMM in all thirteen formats
 // (us, 3-bit uniform g64 at m = 2 / 8 / 16: 11008x4096 8.4 / 9.0 / 9.9 against 9.2 / 15.7 /
 // 15.8; 4096x4096 4.9 / 5.5 / 6.2 against 5.5 / 8.7 / 8.7). Rows of more than 32 chunks
@@ -36,7 +46,11 @@ inline bool skinny_applies(const qx_desc* d, int m) {
   const bool cb = d->kind == QX_CODEBOOK, q4x = d->kind == QX_Q4X;
   if (m > 16) {  // 16-row activation tiles in turn, every code decoded again for each
     const int rf = d->n >= 8192 ? 3 : 1;
-    return J == 1 && (d->n + 16 * rf - 1) / (16 * rf) <= 256 && !q4x && !(cb && d->bits == 4 && d->group <= 64);
+    if (J > 1 || (d->n + 16 * rf - 1) / (16 * rf) > 256 || q4x || (cb && d->bits == 4 && d->group <= 64)) return false;
+    if (m <= 32) return true;
+    if (!third_tile(d->bits, d->kind, d->group) || d->n > 4096 || C <= 28) return false;
+    if (cb ? d->bits == 4 : d->bits == 3 || d->group == 32) return m <= (d->n >= 2048 && (cb || C > 30) ? 48 : 40);
+    return C > 30 && m <= 40 && (d->n >= 2048 || (cb && d->group == 128));
   }
   if (cb && d->bits == 4) {
     if (d->group == 128) return true;

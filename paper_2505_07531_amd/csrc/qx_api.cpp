@@ -248,7 +248,7 @@ int qx_gemm(const qx_desc* d, const void* packed, int32_t m, const uint16_t* X, 
   if (packed == nullptr || X == nullptr || Y == nullptr) return QX_E_ARG;
   if (!aligned16(packed) || !aligned16(X) || !aligned2(Y)) return QX_E_ARG;
   if (m == 1 && qx::gemv_multi_applies(d, 1)) return qx::launch_gemv(d, packed, X, Y, stream);
-  if ((m > 32 || !qx::gemm_skinny_applies(d, m)) && qx::gemm_tile_applies(d, m, false))
+  if (!qx::gemm_skinny_applies(d, m) && qx::gemm_tile_applies(d, m, false))
     return qx::launch_gemm_tile(d, packed, m, X, nullptr, Y, stream);
   // a few rows: the GEMV's chunk-per-lane loads with the products on the matrix cores
   if (qx::gemm_skinny_applies(d, m)) return qx::launch_gemm_skinny(d, packed, m, X, Y, stream);

@@ -44,6 +44,8 @@ CASES = [
     (2, 37, 11008),     # m = 2 on 3 items (uniform and codebook codes here since the one-item look-ahead)
     (2, 20, 16384),     # m = 2 on 4 items: codebooks here, uniform codes GEMV-style
     (24, 130, 4096),    # two activation tiles, the second of 8 rows
+    (33, 2050, 4096),   # three, the last of one row (all but codebook g32, codebook-4 g64 and Q4X)
+    (48, 4090, 3968),   # three, C = 31 (uniform-3, uniform-4 g32, codebook-4 g128)
     (33, 8200, 4096),   # three tiles (the last of one row), three row fragments per wave
     (64, 40, 384),      # four full tiles, one wave
     (47, 8193, 1152),   # three tiles, three fragments, one row in the last block

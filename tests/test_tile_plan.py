@@ -68,3 +68,17 @@ def test_short_and_tall_products_of_few_rows(tile_model):
     # the sizes by which test_gpu_tile.py runs that kernel in every format
     edges = [(f, 0, n, k, m) for f in FORMATS for n, k, m in ((12305, 640, 21), (12309, 1024, 50))]
     assert set(routes(tile_model, edges)) == {"gemm"}
+
+
+def test_third_activation_tile_of_the_small_batch_kernel(tile_model):
+    """33 to 48 rows on small matrices of 29 to 32 chunks stay with gemm_skinny.hip where it
+    measured faster (us there / in the tiled shape that had taken them)."""
+    small = {("c4g128", 0, 4096, 4096, 33): (10.2, 12.0), ("c4g128", 0, 4096, 4096, 48): (10.9, 11.7),
+             ("u3g64", 0, 4096, 4096, 33): (9.2, 10.4), ("c3g128", 0, 2048, 4096, 40): (8.4, 9.2),
+             ("u4g32", 0, 3072, 4096, 40): (9.3, 10.0), ("u3g64", 0, 1376, 3840, 33): (8.2, 9.3), ("u4g128", 0, 4096, 4096, 40): (9.8, 10.3)}
+    got = dict(zip(small, routes(tile_model, small)))
+    assert all(r == "skinny" for r in got.values()), got
+    # slower there (12.0 / 10.9, 10.3 / 10.2, 9.1 / 8.9, 9.4 / 8.9, 19.1 / 14.4), and 49 rows and more
+    keep = [("c3g32", 0, 4096, 4096, 33), ("u4g128", 0, 4096, 4096, 48), ("u4g128", 0, 1376, 4096, 40),
+            ("c3g128", 0, 3072, 3712, 48), ("c3g128", 0, 8192, 4096, 40), ("c4g128", 0, 4096, 4096, 49)]
+    assert all(r in "EFGH" for r in routes(tile_model, keep))
