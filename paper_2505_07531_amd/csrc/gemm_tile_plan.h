@@ -134,13 +134,21 @@ constexpr int per_unit() {  // blocks that fit a compute unit: LDS, and two or t
 }
 
 // Cost of the heavier decoders over that of uniform codes on shapes C, D and E (the same
-// sweep): 16-entry tables, tables of 32 or 64 codes, group sums.
+// sweep): 16-entry tables, tables of 32 or 64 codes.
 template <int BITS, int KIND, int G, bool A8>
 constexpr float decode_factor() {
   if (KIND == QX_Q4X) return 1.4f;
   if (KIND == QX_CODEBOOK)
     return (BITS == 4 ? (G == 32 ? 1.5f : G == 64 ? 1.35f : 1.2f) : G == 32 ? 1.2f : 1.f) * (A8 ? 1.08f : 1.f);
-  return A8 ? (G == 32 ? 1.36f : 1.1f) : 1.f;
+  return 1.f;
+}
+
+// A cost given for 32 chunks, at the matrix's chunks: 6 us of it fixed, with the scaled group
+// sums of uniform codes 16 % of it (start and end of every round of blocks: shape D on 8192 rows
+// at m = 1000, uniform-3 g128 at 8 / 32 / 86 chunks 36 / 94 / 228 us, C at m = 600 31 / 88).
+template <int BITS, int KIND, int G, bool A8>
+float at_chunks(float us, float chunks) {
+  return A8 && KIND == QX_UNIFORM ? us * (0.16f + 0.02625f * chunks) : 6.f + (us - 6.f) * chunks / 32.f;
 }
 
 template <int BITS, int KIND, int G, bool A8, int S>
@@ -149,8 +157,9 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
     constexpr int per = per_unit<BITS, KIND, G, S>();
     const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
     const long rest = blocks % (256 * per);
-    const float us = decode_factor<BITS, KIND, G, A8>() *
-                     ((float)(blocks / (256 * per)) * kShape[S].us[per - 1] + (rest ? kShape[S].us[(rest - 1) / 256] : 0.f));
+    const float us32 = decode_factor<BITS, KIND, G, A8>() *
+                       ((float)(blocks / (256 * per)) * kShape[S].us[per - 1] + (rest ? kShape[S].us[(rest - 1) / 256] : 0.f));
+    const float us = at_chunks<BITS, KIND, G, A8>(us32, (float)(d->k / 128));
     if (us < best) {
       best = us;
       shape = S;
@@ -169,22 +178,31 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
 //     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
 //     122 / 223 here), up to 256 tiles split over k (25 us), 0.05 us a tile up to 512 tiles
 //     of long rows (8-wave blocks);
-//   int8 activations, uniform: 64 x 64 tiles, 0.053 us a tile (11008x4096 uniform-3 g64 at
-//     m = 256 / 512 / 1024 / 2048: 56 / 96 / 164 / 318 us against 64 / 86 / 132 / 247 here),
-//     and 22 us more for rows of up to 64 chunks, which have 4-wave blocks.
+//   int8 activations, uniform: 64 x 64 tiles, 1.5 ns times q a tile and chunk and 6 us, in the unit
+//     of the shapes' costs, whose group sums take the same factor of 1.1 to 1.3 in all of them; q and
+//     at_chunks fitted to 720 sizes (n = 1000 to 22016, k = 1024 to 11008, m = 200 to 2048), of which
+//     11 then lose 3 % or more (14 % at most). 8192 rows, m = 1000, 2048 tiles, 8 / 32 / 86 chunks, us there
+//     and here: 3-bit g128 31 / 36, 105 / 98, 246 / 228; g32 44 / 38, 144 / 107, 311 / 266.
+// `share` of it, at the matrix's chunks.
 template <int BITS, int KIND, int G, bool A8>
-float other_cost(const qx_desc* d, int m) {
+float other_cost(const qx_desc* d, int m, float share) {
+  const float chunks = (float)(d->k / 128);
+  const auto at = [&](float us) { return at_chunks<BITS, KIND, G, A8>(share * us, chunks); };
   const bool wide = d->k > 64 * 128;
   const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
   if (KIND != QX_UNIFORM)
-    return (t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
-           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f);
-  if (A8) return (0.053f * (float)t64 + (wide ? 0.f : 22.f)) * (G == 32 ? 1.25f : 1.f);
+    return at((t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
+           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f));
+  if (A8)
+    return 6.f + 0.0015f * chunks * (float)t64 *
+                     (G == 32 ? (wide ? 0.8f : 1.f) * (BITS == 3 ? 1.24f : 1.48f)
+                              : (wide && BITS == 3 && G == 64 ? 0.9f : 1.f) *
+                                    (BITS == 3 ? (G == 64 ? 1.f : 0.91f) : G == 64 ? 1.09f : 1.03f));
   const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
-  if (t128 <= 256) return t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f;
-  if (m >= 384) return 76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256);
+  if (t128 <= 256) return at(t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f);
+  if (m >= 384) return at(76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256));
   const long rest = t128 % 768;
-  return 74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f);
+  return at(74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f));
 }
 
 // Split over k: every block's time is its fixed part and its chunks.
@@ -250,23 +268,19 @@ template <int BITS, int KIND, int G, bool A8>
 int pick(const qx_desc* d, int m) {
   // 17 to 64 rows: one of these shapes unless small_tiles_win; qx_gemm keeps up to 32 rows of
   // up to 32 chunks with gemm_skinny.hip where that applies (4096x4096 uniform-4 at m = 19:
-  // 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28: 15.1 and 17.1). Above, a shape
-  // must promise 4 % less than the other kernel (12 %
-  // against the integer products, whose fit is coarser: 2146x2432 uniform-3 g128 at m = 2436
-  // 54 us there, 64 here), as much as the costs may be off.
-  const float chunks = (float)(d->k / 128);
+  // 8.1 us there, 9.6 here; 12288x4096 codebook-3 at m = 28: 15.1 and 17.1). Above, a shape must
+  // promise 4 % less than gemm.hip; the fit for the integer products of gemm_a8.hip weighs both.
   float best = 1e30f;
   int shape = kShapes;
   if (m <= 64 && (!A8 || KIND != QX_UNIFORM) && small_tiles_win<BITS, KIND, G, A8>(d, m)) return shape;
   if (m > 64) {
-    best = (A8 && KIND == QX_UNIFORM ? 0.88f : 0.96f) * other_cost<BITS, KIND, G, A8>(d, m);
+    best = other_cost<BITS, KIND, G, A8>(d, m, 0.96f);
     consider<BITS, KIND, G, A8, kA>(d, m, best, shape);
     consider<BITS, KIND, G, A8, kB>(d, m, best, shape);
     consider<BITS, KIND, G, A8, kC>(d, m, best, shape);
     consider<BITS, KIND, G, A8, kD>(d, m, best, shape);
   }
   if (m > 32 && (m > 64 || !A8 || KIND != QX_UNIFORM)) consider<BITS, KIND, G, A8, kE>(d, m, best, shape);
-  if (best < 1e30f) best = 6.f + (best - 6.f) * chunks / 32.f;  // us at this k (6 us of them fixed)
   consider_split<BITS, KIND, G, A8, kF>(d, m, best, shape);
   consider_split<BITS, KIND, G, A8, kG>(d, m, best, shape);
   consider_split<BITS, KIND, G, A8, kH>(d, m, best, shape);

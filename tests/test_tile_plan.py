@@ -82,3 +82,18 @@ def test_third_activation_tile_of_the_small_batch_kernel(tile_model):
     keep = [("c3g32", 0, 4096, 4096, 33), ("u4g128", 0, 4096, 4096, 48), ("u4g128", 0, 1376, 4096, 40),
             ("c3g128", 0, 3072, 3712, 48), ("c3g128", 0, 8192, 4096, 40), ("c4g128", 0, 4096, 4096, 49)]
     assert all(r in "EFGH" for r in routes(tile_model, keep))
+
+
+def test_int8_rows_of_uniform_weights(tile_model):
+    """More than 64 int8 rows: sizes at which gemm_a8.hip measured faster than the tiled shape
+    that had taken them (us there / in that shape)."""
+    there = {("u3g128", 1, 8192, 4096, 600): (69.9, 88.4), ("u4g128", 1, 8192, 4096, 600): (70.7, 77.6),
+             ("u3g64", 1, 8192, 1024, 600): (24.2, 29.9), ("u4g128", 1, 22016, 1024, 600): (52.1, 62.5),
+             ("u3g128", 1, 2000, 4096, 2048): (54.0, 60.2), ("u4g64", 1, 4096, 1024, 1000): (19.4, 22.2)}
+    got = dict(zip(there, routes(tile_model, there)))
+    assert all(r == "gemm_a8" for r in got.values()), got
+    # faster in a tiled shape (us in gemm_a8.hip / there)
+    here = {("u3g64", 1, 11008, 4096, 512): (96, 86), ("u4g128", 1, 11008, 4096, 1000): (207, 119),
+            ("u3g32", 1, 22016, 1024, 2048): (212, 178), ("u4g32", 1, 4096, 4096, 1000): (83, 66)}
+    got = dict(zip(here, routes(tile_model, here)))
+    assert all(r in "ABCDE" for r in got.values()), got
