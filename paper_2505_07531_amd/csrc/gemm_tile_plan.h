@@ -176,8 +176,9 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
 //     256 / 500: 20.6 / 25.8 / 37.6 us);
 //   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
 //     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
-//     122 / 223 here), up to 256 tiles split over k (25 us), 0.05 us a tile up to 512 tiles
-//     of long rows (8-wave blocks);
+//     122 / 223 here), up to 256 tiles split over k (25 us); 257 to 512 are one round of two
+//     blocks a unit, 44 us (512 tiles, us there and in shape E: codebook-4 g128 44 / 48,
+//     codebook-3 g128 41 / 38, g32 44 / 46), of long rows (8-wave blocks) 0.05 us a tile;
 //   int8 activations, uniform: 64 x 64 tiles, 1.5 ns times q a tile and chunk and 6 us, in the unit
 //     of the shapes' costs, whose group sums take the same factor of 1.1 to 1.3 in all of them; q and
 //     at_chunks fitted to 720 sizes (n = 1000 to 22016, k = 1024 to 11008, m = 200 to 2048), of which
@@ -191,7 +192,7 @@ float other_cost(const qx_desc* d, int m, float share) {
   const bool wide = d->k > 64 * 128;
   const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
   if (KIND != QX_UNIFORM)
-    return at((t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
+    return at((t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : t64 <= 512 && !wide && !(A8 && BITS == 3 && G == 32 && chunks < 16.f) ? 44.f : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
            (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f));
   if (A8)
     return 6.f + 0.0015f * chunks * (float)t64 *

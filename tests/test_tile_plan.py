@@ -97,3 +97,15 @@ def test_int8_rows_of_uniform_weights(tile_model):
             ("u3g32", 1, 22016, 1024, 2048): (212, 178), ("u4g32", 1, 4096, 4096, 1000): (83, 66)}
     got = dict(zip(here, routes(tile_model, here)))
     assert all(r in "ABCDE" for r in got.values()), got
+
+
+def test_table_formats_with_one_round_of_64x64_tiles(tile_model):
+    """257 to 512 tiles of 64 x 64 in rows of up to 64 chunks: us in gemm.hip / in shape E."""
+    there = {("c4g128", 0, 8192, 4096, 200): (43.5, 48.7), ("c4g128", 0, 2000, 4096, 1000): (43.6, 48.4),
+             ("c3g32", 0, 8192, 4096, 200): (43.8, 46.5), ("c4g64", 1, 2000, 4096, 1000): (51.8, 57.9),
+             ("q4x", 1, 8192, 1024, 200): (18.0, 20.4), ("c4g128", 1, 8192, 4096, 200): (49.1, 52.0)}
+    got = dict(zip(there, routes(tile_model, there)))
+    assert all(r == "gemm" for r in got.values()), got
+    here = {("c3g128", 0, 8192, 4096, 200): (40.6, 38.1), ("c4g32", 0, 11008, 4096, 96): (68.6, 67.3)}
+    got = dict(zip(here, routes(tile_model, here)))
+    assert all(r == "E" for r in got.values()), got
