@@ -525,7 +525,7 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
         const long mb = (m + 127) / 128;
         const long big = (long)((d->n + 191) / 192) * mb, big8 = (long)((d->n + 255) / 256) * mb;
         const long last = big % 256 == 0 ? 256 : big % 256;
-        constexpr bool kBig8 = !(BITS == 3 && G == 32);
+        constexpr bool kBig8 = kGemmBig8<BITS, G>;
         if (kBig8 && QX_GEMM_CFG == 0 && m >= 384 && (big8 + 255) / 256 < (big + 255) / 256) {
           if constexpr (kBig8)
             launch_gemm_cfg<BITS, KIND, G, 8, 2, 1, QX_GEMM_BIG_S, QX_GEMM_BIG_DX, A8, 8>(d, p, m, X, sx, Y, s);

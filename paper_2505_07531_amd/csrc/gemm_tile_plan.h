@@ -171,7 +171,9 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
 // fitted to their times in the sweep:
 //   fp16 activations, uniform: 128 x 256 blocks at 76 us a round from m = 384 (11008x4096
 //     uniform-4 g128 at m = 512 / 1024 / 2048: 77 / 142 / 227 us), 128 x 64 tiles that take
-//     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54);
+//     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54), for
+//     3-bit g32, which has no others, 55 to 58 and 83 to 86 us for two and three of them on a
+//     unit (4096 rows, m = 600 and 1000; 5504 at m = 768) against 53 to 54 and 72 to 78 in E or C;
 //     up to 64 / 128 / 256 tiles of 128 x 64 are split over k (4096x4096 uniform-4 at m = 100 /
 //     256 / 500: 20.6 / 25.8 / 37.6 us);
 //   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
@@ -201,9 +203,10 @@ float other_cost(const qx_desc* d, int m, float share) {
                                     (BITS == 3 ? (G == 64 ? 1.f : 0.91f) : G == 64 ? 1.09f : 1.03f));
   const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
   if (t128 <= 256) return at(t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f);
-  if (m >= 384) return at(76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256));
+  if (kGemmBig8<BITS, G> && m >= 384) return at(76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256));
   const long rest = t128 % 768;
-  return at(74.f * (float)(t128 / 768) + (rest ? kShape[kE].us[(rest - 1) / 256] : 0.f));
+  constexpr float us[3] = {41.f, kGemmBig8<BITS, G> ? 54.f : 57.f, kGemmBig8<BITS, G> ? 74.f : 85.f};
+  return at(us[2] * (float)(t128 / 768) + (rest ? us[(rest - 1) / 256] : 0.f));
 }
 
 // Split over k: every block's time is its fixed part and its chunks.

@@ -51,6 +51,11 @@ int launch_gemm_lut_a8(const qx_desc* d, const void* packed, int m, const int8_t
 int launch_gemv_a8q(const qx_desc* d, const void* packed, const int8_t* xq, const float* sx, uint16_t* y,
                     hipStream_t s);
 
+// Whether gemm.hip has 128 x 256 blocks of 8 waves for uniform weights (m >= 384): not for
+// 3-bit g32, whose 8-wave tile spills.
+template <int BITS, int G>
+constexpr bool kGemmBig8 = !(BITS == 3 && G == 32);
+
 // Products of more than 16 rows in larger wave tiles, or with k split over a block's waves
 // (gemm_tile.hip), where gemm_tile_applies expects less time than from the other kernels: X fp16 [m][k] with sx null, or the
 // int8 rows of qx_quantize_a8 with their scales.

@@ -109,3 +109,14 @@ def test_table_formats_with_one_round_of_64x64_tiles(tile_model):
     here = {("c3g128", 0, 8192, 4096, 200): (40.6, 38.1), ("c4g32", 0, 11008, 4096, 96): (68.6, 67.3)}
     got = dict(zip(here, routes(tile_model, here)))
     assert all(r == "E" for r in got.values()), got
+
+
+def test_uniform_3_bit_g32_against_blocks_it_has(tile_model):
+    """gemm.hip has no 128 x 256 blocks for 3-bit codes in groups of 32: its products are compared
+    with the 128 x 64 tiles that run (us there / in the tiled shape)."""
+    sizes = {("u3g32", 0, 11008, 4096, 600): (106, 79), ("u3g32", 0, 4096, 4096, 2048): (119, 88),
+             ("u3g32", 0, 16384, 4096, 512): (110, 85), ("u3g32", 0, 8192, 11008, 1000): (292, 218),
+             ("u3g32", 0, 11008, 4096, 300): (55.8, 54.8), ("u3g32", 0, 4096, 4096, 600): (55.5, 53.6)}
+    got = dict(zip(sizes, routes(tile_model, sizes)))
+    assert all(r in "ABCDE" for r in got.values()), got
+    assert routes(tile_model, [("u3g32", 0, 4096, 4096, 400)]) == ["gemm"]  # 39.1 there, 41.0 in E
