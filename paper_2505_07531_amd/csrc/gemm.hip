@@ -454,27 +454,20 @@ static void launch_gemm_cfg(const qx_desc* d, const char* p, int m, const void* 
 
 // Tile shape per activation row count (from a sweep of MT, NT, KS, S, DX on the
 // 3-bit g64 MLP shapes at m = 16, 64, 512, and at m = 128-512 a split of k when
-// the tiles are few: uniform 4096x11008 at m = 128 took 113 us whole and 57 us
-// split four ways, codebook-3 78 and 55 us split two ways). Small m is bound by streaming the codes:
+// the tiles are few: uniform 4096x4096 at m = 256 25.8 us split two ways, codebook-4 g32 and Q4X
+// likewise). Small m is bound by streaming the codes:
 // one 16-row activation tile, 16 weight rows per block and the chunks of a row
 // split over the four waves, so that the grid has enough blocks. Larger m gets
 // larger activation tiles so that each decoded weight feeds more MFMAs; with
-// m > 64 a wave owns 64 activation x 32 weight rows.
-#ifndef QX_GEMM_CFG
-#define QX_GEMM_CFG 0  // 0: by m; 1, 2, 4 force one shape
-#endif
+// m > 64 a wave owns 64 activation x 32 weight rows. Beyond 16 rows gemm_tile.hip takes the
+// products that its shapes do in less time (gemm_tile_plan.h), and only the forms that the
+// rest can reach are built.
 #ifndef QX_GEMM_BIG_W
 // m > 64, rows of more than 64 chunks, 129-256 tiles (one block of 8 waves per compute
 // unit): k split over 2 of 8 waves instead of walked by one (4096x11008 at m = 512:
 // uniform-3 122.7 -> 98.4 us, uniform-4 101.2 -> 84.4; codebook-3 at m = 256 78.6 ->
 // 61.8, but 112.7 -> 120.3 at m = 512, 512 tiles); 4 keeps the 4-wave shapes
 #define QX_GEMM_BIG_W 8
-#endif
-#ifndef QX_GEMM_BIG_S
-#define QX_GEMM_BIG_S 4  // super-round (rounds per code load) of the 128 x 192 blocks
-#endif
-#ifndef QX_GEMM_BIG_DX
-#define QX_GEMM_BIG_DX 1  // activation rounds in flight of the 128 x 192 blocks (11008x4096 u3g64 m = 512: 95.1 us with 2, 89.8 with 1)
 #endif
 #ifndef QX_GEMM_SMALL_W
 #define QX_GEMM_SMALL_W 4  // 4: waves per block for m <= 16 by shape; 8, 16 force (sweeps)
@@ -484,8 +477,7 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
                          uint16_t* Y, hipStream_t s) {
   const char* p = static_cast<const char*>(packed);
   constexpr bool kUni = KIND == QX_UNIFORM;
-  const int cfg = QX_GEMM_CFG > 0 ? QX_GEMM_CFG : m <= 16 ? 1 : m <= 64 ? 2 : 4;
-  switch (cfg) {
+  switch (m <= 16 ? 1 : m <= 64 ? 2 : 4) {
     case 1: {
       // rows of more than 64 chunks: the k split over 8 waves (codebook, Q4X) or 16
       // (uniform, m <= 8), each walking fewer chunks; 4096x11008 at m = 16 took 24.7 us
@@ -506,41 +498,36 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
     }
     case 2:
       // 17 to 64 rows: several rounds of tiles, or short rows (small_tiles_win in gemm_tile_plan.h)
-      launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, kUni ? 1 : 2, A8>(d, p, m, X, sx, Y, s);
+      if constexpr (!(A8 && BITS == 3 && G > 32)) launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, kUni ? 1 : 2, A8>(d, p, m, X, sx, Y, s);
+      else return QX_E_UNSUPPORTED;  // int8 rows of codebook-3 g64 and g128 always take gemm_tile.hip
       break;
     default:
       if constexpr (kUni) {
         // few 128 x 64 tiles (e.g. 4096 weight rows at m <= 256): split k over the waves
         const long tiles = (long)((d->n + 127) / 128) * ((m + 63) / 64);
-        // many rows: 128 x 48 per wave (each decoded fragment feeds 8 products) in
-        // 128 x 192 blocks, one per compute unit, where the last round of blocks keeps
-        // most units busy (11008x4096 uniform-3 at m = 512: 110 -> 91 us, m = 1024 193
-        // -> 165; 22016x4096 m = 512 183 -> 163; but 11008 rows at m = 768, two rounds
-        // with 92 blocks in the second, 166 against 167). 128 x 32 per wave in 128 x 256
-        // blocks of 8 waves (two per SIMD: about 30 % more work per compute unit in the
-        // same time) where those take fewer rounds of blocks (11008x4096 uniform-3 g64 at
-        // m = 2048: 298.7 -> 248.3 us, 12288x4096 299.6 -> 255.0, 22016x4096 at m = 1024
-        // 297.5 -> 241.0; with as many rounds, e.g. 11008 rows at m = 512, 76.8 against
-        // 79.3 for the 4-wave blocks). Not for 3-bit g32, whose 8-wave tile spills.
+        // many rows: 128 x 32 per wave in 128 x 256 blocks of 8 waves, two per SIMD, where
+        // those take fewer rounds of blocks than 128 x 192 blocks of 4 waves (11008x4096
+        // uniform-3 g64 at m = 2048: 248.3 us, 298.7 in those; 22016x4096 at m = 1024 241.0
+        // and 297.5). Where they take as many, the shape of gemm_tile.hip with 128 x 192
+        // blocks is the faster one.
         const long mb = (m + 127) / 128;
         const long big = (long)((d->n + 191) / 192) * mb, big8 = (long)((d->n + 255) / 256) * mb;
-        const long last = big % 256 == 0 ? 256 : big % 256;
         constexpr bool kBig8 = kGemmBig8<BITS, G>;
-        if (kBig8 && QX_GEMM_CFG == 0 && m >= 384 && (big8 + 255) / 256 < (big + 255) / 256) {
-          if constexpr (kBig8)
-            launch_gemm_cfg<BITS, KIND, G, 8, 2, 1, QX_GEMM_BIG_S, QX_GEMM_BIG_DX, A8, 8>(d, p, m, X, sx, Y, s);
-        } else if (QX_GEMM_CFG == 0 && m >= 384 && last >= 150)
-          launch_gemm_cfg<BITS, KIND, G, 8, 3, 1, QX_GEMM_BIG_S, QX_GEMM_BIG_DX, A8>(d, p, m, X, sx, Y, s);
-        else if (QX_GEMM_CFG == 0 && tiles <= 64) launch_gemm_cfg<BITS, KIND, G, 4, 2, 4, 1, 1, A8>(d, p, m, X, sx, Y, s);
-        else if (QX_GEMM_CFG == 0 && tiles <= 128) launch_gemm_cfg<BITS, KIND, G, 4, 2, 2, 4, 2, A8>(d, p, m, X, sx, Y, s);
+        if (kBig8 && m >= 384 && (big8 + 255) / 256 < (big + 255) / 256) {
+          if constexpr (kBig8) launch_gemm_cfg<BITS, KIND, G, 8, 2, 1, 4, 1, A8, 8>(d, p, m, X, sx, Y, s);
+        } else if (tiles <= 128)
+          launch_gemm_cfg<BITS, KIND, G, 4, 2, 2, 4, 2, A8>(d, p, m, X, sx, Y, s);
         else if (QX_GEMM_BIG_W == 8 && d->k > 64 * 128 && tiles <= 256)
           launch_gemm_cfg<BITS, KIND, G, 4, 2, 2, 4, 2, A8, 8>(d, p, m, X, sx, Y, s);
         else launch_gemm_cfg<BITS, KIND, G, 4, 2, 1, 4, 2, A8>(d, p, m, X, sx, Y, s);
       } else {
-        // codebook and Q4X: 64 x 64 tiles; at most 128 of them split k over two waves
+        // codebook and Q4X: 64 x 64 tiles; at most 128 of them split k over two waves (the
+        // lighter decoders' products of so few tiles all take gemm_tile.hip)
         const long tiles = (long)((d->n + 63) / 64) * ((m + 63) / 64);
-        if (QX_GEMM_CFG == 0 && tiles <= 128) launch_gemm_cfg<BITS, KIND, G, 4, 1, 2, 4, 2, A8>(d, p, m, X, sx, Y, s);
-        else if (QX_GEMM_BIG_W == 8 && d->k > 64 * 128 && tiles <= 256 && !(BITS == 4 && G == 32)) {
+        constexpr bool kSplit = KIND == QX_Q4X || (BITS == 4 && G < 128);
+        if (kSplit && tiles <= 128) {
+          if constexpr (kSplit) launch_gemm_cfg<BITS, KIND, G, 4, 1, 2, 4, 2, A8>(d, p, m, X, sx, Y, s);
+        } else if (QX_GEMM_BIG_W == 8 && d->k > 64 * 128 && tiles <= 256 && !(BITS == 4 && G == 32)) {
           if constexpr (!(BITS == 4 && G == 32))  // 32-code tables of 16 entries overflow LDS at 8 waves
             launch_gemm_cfg<BITS, KIND, G, 4, 1, 2, 4, 2, A8, 8>(d, p, m, X, sx, Y, s);
         } else {

@@ -122,6 +122,9 @@ template <int BITS, int KIND, int G, bool A8>
 constexpr bool built(int s) {
   if (s == kA) return kLight<BITS, KIND, G, A8> && !A8;
   if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && BITS == 4 && G == 32);
+  // D is at no size the cheapest by the costs below with these codebooks, whose tables leave room
+  // for one block of it on a compute unit, but for two of E
+  if (s == kD) return !(KIND == QX_CODEBOOK && ((BITS == 3 && G == 32) || (BITS == 4 && G == 64)));
   if (s >= kF) return (KIND != QX_UNIFORM || !A8) && !(s == kF && KIND == QX_CODEBOOK && BITS == 4 && G == 32);
   return true;
 }
