@@ -1,6 +1,8 @@
-"""The tiled GEMM (more than 16 activation rows) against plain products in 64 bits:
-every block shape and format, chunk counts 1, 2, 3 and odd ones, partial tiles in both
-directions, rows of Y at odd offsets (n % 4 != 0) and at a misaligned pointer.
+"""The tiled GEMM (more than 16 activation rows) against plain products in 64 bits: every
+block shape that is built, in every format, with fp16 and with int8 activations
+(test_tile_plan.py checks on the CPU that the sizes here select each of them), chunk counts
+1, 2, 3 and odd ones, partial tiles in both directions, rows of Y at odd offsets
+(n % 4 != 0) and at a misaligned pointer.
 
 Tolerance: fp16 outputs of fp32 sums. An output carries its own rounding, 2^-11 of it, and
 at most k + 2 fp32 roundings of partial sums, bounded by 2^-24 (k + 2) sum |w x|; with fp16
@@ -14,15 +16,24 @@ pytestmark = pytest.mark.gpu
 
 U3, U4, C3, C4 = (3, 0), (4, 0), (3, 1), (4, 1)
 FORMATS = [(*f, g) for f in (U3, U4, C3, C4) for g in (32, 64, 128)] + [(4, 2, 64)]
-# Sizes that the cost model gives to each shape in one format or another (k does not enter
-# for k <= 8192): few blocks, one and more rounds of blocks, last blocks of 1 or few rows;
-# then the shapes that split k over a block's waves, with fewer chunks than waves, as many,
-# and numbers that leave some waves one chunk short.
+# Few blocks, one and more rounds of blocks, last blocks of 1 or few rows; the shapes that
+# split k over a block's waves with fewer chunks than waves, as many, and numbers that leave
+# some waves one chunk short.
 SIZES = [(500, 128, 70), (1376, 1024, 77), (4001, 1408, 40), (1001, 1152, 17), (333, 11008, 65), (4096, 11008, 100),
          (11008, 256, 64), (4099, 128, 500), (11009, 384, 258), (11008, 256, 521), (5506, 640, 1025), (22013, 256, 1030),
          (4096, 128, 2048),
          # 17 to 64 rows in the 32 x 32 tiles of gemm.hip (fp16): an odd number of chunks, one and two tiles
-         (12305, 640, 21), (12309, 1024, 50)]
+         (12305, 640, 21), (12309, 1024, 50),
+         # with odd chunk counts, the shapes (and the remaining forms of gemm.hip) that the ones above leave out
+         (228, 1408, 2063), (234, 384, 2087), (2208, 384, 2189), (201, 384, 1261), (456, 384, 2125), (225, 2432, 2162),
+         (4868, 384, 1590), (344, 9088, 2081), (7577, 384, 2061), (521, 8576, 1997)]
+# int8 rows of uniform weights: the sizes at which a shape is taken instead of gemm_a8.hip
+UNIFORM_A8 = [(4283, 896, 1868), (1884, 1408, 2118), (2723, 2176, 2166), (2023, 2944, 2026), (4311, 1152, 1911),
+              (6086, 1920, 2002), (2888, 6784, 2089)]
+
+
+def sizes(fmt, a8):
+    return SIZES + (UNIFORM_A8 if a8 and fmt[1] == 0 else [])
 
 
 def quant(fmt, n, k):
@@ -72,7 +83,7 @@ def check(y, x, w):
 def test_tile_shapes(gpu, fmt, a8):
     import torch
     qx, dev = gpu, "cuda"
-    for n, k, m in SIZES:
+    for n, k, m in sizes(fmt, a8):
         print(f"tile {fmt} a8={a8} {n}x{k} m={m}", flush=True)
         q = quant(fmt, n, k)
         pw = qx.PackedWeight.from_quant(q)

@@ -120,3 +120,20 @@ def test_uniform_3_bit_g32_against_blocks_it_has(tile_model):
     got = dict(zip(sizes, routes(tile_model, sizes)))
     assert all(r in "ABCDE" for r in got.values()), got
     assert routes(tile_model, [("u3g32", 0, 4096, 4096, 400)]) == ["gemm"]  # 39.1 there, 41.0 in E
+
+
+def test_gpu_sizes_reach_every_built_shape(tile_model):
+    """The sizes that test_gpu_tile.py runs select every shape that is built, in every format
+    and with both kinds of activations: a change of the cost model that takes a kernel out of
+    that test's reach, or out of reach altogether, fails here."""
+    from test_gpu_tile import sizes
+    name = {v: f for f, v in FORMATS.items()}
+    built = {}
+    for line in tile_model("reads"):
+        b, kind, g, a8, shape = line.split()[:5]
+        built.setdefault((name[int(b), int(kind), int(g)], int(a8)), set()).add(shape)
+    assert len(built) == 2 * len(FORMATS)
+    for (f, a8), shapes in built.items():
+        b, kind, g = FORMATS[f]
+        got = set(routes(tile_model, [(f, a8, *s) for s in sizes((b, kind, g), a8)]))
+        assert got >= shapes, (f, a8, shapes - got)
