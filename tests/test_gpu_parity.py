@@ -218,10 +218,10 @@ def test_gemm_prefill_shapes(gpu, m, name):
 
 
 # activation tiles mapped to XCDs with padding blocks, single-chunk rows, chunk counts
-# that leave K-split waves idle in the last round; 128 x 192 blocks (uniform formats at
-# m >= 384) with ragged weight and activation rows; 128 x 256 blocks of 8 waves where those
-# take fewer rounds (11000 rows at m = 600: last block of 248 rows, last tile of 88; 16400
-# rows at m = 384)
+# that leave K-split waves idle in the last round; blocks of 128 activation rows with ragged
+# weight and activation rows (9601 rows at m = 390: 128 x 192 of gemm_tile.hip); 128 x 256
+# blocks of 8 waves of gemm.hip in the uniform formats (11000 rows at m = 600: last block of
+# 248 rows, last tile of 88; 16400 rows at m = 384)
 GEMM_EDGES = [(40, 1024, 300), (300, 1152, 100), (17, 128, 129), (70, 640, 40), (1, 640, 17),
               (4096, 1152, 128), (2000, 1536, 200), (9601, 1152, 390), (4800, 640, 768),
               (11000, 640, 600), (16400, 384, 384)]
@@ -256,9 +256,9 @@ def test_gemm_rows_equal_gemv_within_tolerance(gpu):
 @pytest.mark.parametrize("fmt", [(3, 0, 64), (4, 0, 128), (3, 1, 128), (4, 1, 32)], ids=_fmt_id)
 @pytest.mark.parametrize("m", [33, 64, 256, 512])
 def test_gemm_long_rows_wide_split(gpu, fmt, m):
-    """Rows of more than 64 chunks with the k split over 8 waves: at 16 < m <= 64 with enough
-    weight rows that uniform 32 x 32 tiles number more than 128, and at m = 256 / 512 with
-    129-256 tiles (sampled rows against the oracle)."""
+    """Rows of more than 64 chunks: at m = 33 / 64 the k split over 8 waves of gemm_tile.hip, at
+    m = 256 / 512 with 129-256 tiles the one over 2 of 8 waves of gemm.hip (codebooks at
+    m = 512: one round of 64 x 128 blocks of gemm_tile.hip; sampled rows against the oracle)."""
     qx = gpu
     bits, kind, g = fmt
     n, k = (4200 if m <= 64 else 4096), 11008

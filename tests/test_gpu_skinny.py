@@ -1,10 +1,10 @@
-"""Parity of the small-batch matrix-core GEMM (qx_gemm at 2 <= m <= 64) with the oracle.
+"""Parity of the small-batch matrix-core GEMM (qx_gemm at 2 <= m <= 48) with the oracle.
 
 That kernel keeps the GEMV's one-chunk-per-lane loads and multiplies on the
 matrix cores: a block's waves split each row's chunks 4 per wave and item (up
 to 4 items per lane, up to 8 waves) on 16, 32, 48 or 96 weight rows per block
 (one, two, three or six row fragments per wave), each wave stages the m activation rows of
-its chunks in LDS, and the m rows fill 16-row tiles taken in turn (more than one
+its chunks in LDS, and the m rows fill up to three 16-row tiles taken in turn (more than one
 only on rows of at most 32 chunks). Tall matrices with rows of 29-32 chunks at m <= 16
 take a pipelined form instead (one block per compute unit walking 16-row groups with
 two in flight). The cases below take
@@ -46,10 +46,11 @@ CASES = [
     (24, 130, 4096),    # two activation tiles, the second of 8 rows
     (33, 2050, 4096),   # three, the last of one row (all but codebook g32, codebook-4 g64 and Q4X)
     (48, 4090, 3968),   # three, C = 31 (uniform-3, uniform-4 g32, codebook-4 g128)
-    (33, 8200, 4096),   # three tiles (the last of one row), three row fragments per wave
-    (64, 40, 384),      # four full tiles, one wave
-    (47, 8193, 1152),   # three tiles, three fragments, one row in the last block
-    (56, 8200, 4096),   # four tiles (the last of 8 rows), three fragments per wave
+    (17, 8200, 4096),   # two, the last of one row, three row fragments per wave (all but Q4X, codebook-4 g32 and g64)
+    (25, 8193, 1152),   # two, three fragments, 3 waves, one row in the last block
+    (31, 12287, 3840),  # two, three fragments, C = 30, one round of 256 blocks, the last of 47 rows
+    # past the kernel's activation tiles for these shapes, routed elsewhere
+    (33, 8200, 4096), (64, 40, 384), (47, 8193, 1152), (56, 8200, 4096),
     (9, 16400, 1024),   # six row fragments per wave (16384 rows or more), last block of 80 rows
     (2, 8190, 4096),    # pipelined form: two 16-row groups per compute unit, the last of 14 rows
     (16, 16390, 3840),  # pipelined, C = 30 (lane groups past the row), 4-5 groups per block, last of 6 rows
@@ -113,7 +114,7 @@ def test_skinny_one_hot_rows_are_columns(gpu, fmt, m, n, k):
     """Activation row r one-hot at position j_r: row r of Y equals column j_r of W' in
     value (a sum that starts at +0 turns -0 weights into +0), on shapes with 3 items per
     lane and a ragged last item (16-row blocks), with 48-row blocks at m = 16, with three
-    activation tiles at m = 40, and in the pipelined form (16400 rows)."""
+    activation tiles at m = 40 (where the format has them), and in the pipelined form (16400 rows)."""
     qx = gpu
     q = _quant(n, k, fmt, seed=m)
     cols = np.random.default_rng(m + 1).choice(k, m, replace=False)
