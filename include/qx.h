@@ -209,8 +209,9 @@ int qx_quantize_a8(int32_t m, int32_t k, const uint16_t* X, int8_t* Xq, float* s
  *   Xq, sx as qx_quantize_a8 wrote them for the same k; Y fp16 [m][n]
  *   (written, 2-byte aligned), rounded to nearest-even:
  *   uniform: sx[r] * sum_j s_j * sum_{k in group j} (q - z_j) * xq[r][k], the
- *     group sums exact (int8 matrix-core products, int32 accumulation), scaled
- *     in fp32;
+ *     group sums exact and scaled in fp32 (int8 matrix-core products with int32
+ *     accumulation; above 64 rows, by shape, the same integers as fp16 values
+ *     with fp32 accumulation, a group of 128 as two halves each scaled);
  *   codebook: sx[r] * sum_k C_j[q] * xq[r][k] on the fp16 matrix cores (the
  *     table entries and the codes xq as exact fp16 values, fp32 accumulation),
  *     scaled in fp32;
@@ -229,7 +230,7 @@ int qx_gemm_a8(const qx_desc* d, const void* packed, int32_t m, const int8_t* Xq
  *   X fp16 [m][k] row-major; Y fp16 [m][n] row-major (written; 2-byte
  *   alignment suffices for Y). fp16 products, fp32 accumulate, RNE to fp16:
  *   on the matrix cores with W' decoded exactly into their operands (for a few
- *   rows, m <= 32 by shape and format, each lane decoding its own chunks as in
+ *   rows, m <= 48 by shape and format, each lane decoding its own chunks as in
  *   the GEMV), or, for m <= 4 where that measured faster, GEMV-style with every
  *   code decoded once for all rows. m = 0 or n = 0 is a no-op; m must be
  *   <= 65536. All formats, Q4X included. Deterministic.

@@ -44,7 +44,8 @@
 // A8: X holds int8 codes (qx_quantize_a8), which enter the products as exact binary16
 // integers; Y is scaled by the row's sx. Uniform and Q4X weights then enter as the exact
 // integers q - z or the sub-codebook's entries, and the sum of a group (of half a group of
-// 128) is scaled by its s in fp32: at most 64 * 15 * 127 for uniform codes, exact in fp32.
+// 128) is scaled by its s in fp32. The products are exact; so are the sums of uniform codes (at
+// most 64 * 15 * 127), those of Q4X round as fp32 sums do.
 #include <type_traits>
 
 #include "gemm_tile_plan.h"

@@ -110,7 +110,8 @@ constexpr ShapeCost kShape[kShapes] = {
     {32, 32, 2, 2, 1, 1, {3.8f, 0.19f, 0.74f}, 8},
 };
 
-// Formats whose decoding leaves the registers of the 128 x 64 wave tile unspilled.
+// Formats whose decoding leaves the 128 x 64 wave tile enough registers: unspilled but for int8
+// rows of codebook-3, which spill 16 (g64) and 6 (g128) and are the faster shape all the same.
 template <int BITS, int KIND, int G, bool A8>
 constexpr bool kLight = KIND == QX_UNIFORM ? !A8 : KIND == QX_CODEBOOK && BITS == 3 && G >= 64;
 
