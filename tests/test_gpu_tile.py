@@ -97,18 +97,22 @@ def test_tile_shapes(gpu, fmt, a8):
         del pw
 
 
-@pytest.mark.parametrize("n", [4099, 4100])
-def test_tile_output_offset(gpu, n):
-    """Y may start at any multiple of 2 bytes; what lies around it stays untouched."""
+@pytest.mark.parametrize("m", [50, 500])  # k split over waves, and one round of blocks
+@pytest.mark.parametrize("n", [4097, 4098, 4099, 4100])
+def test_tile_output_offset(gpu, n, m):
+    """Y may start at any multiple of 2 bytes, and with it every row and its stores of 8 bytes;
+    what lies around it stays untouched."""
     import torch
-    qx, dev, m, k = gpu, "cuda", 500, 256
+    qx, dev, k = gpu, "cuda", 256
     pw = qx.PackedWeight.from_quant(quant((4, 0, 64), n, k))
     X = torch.randn(m, k, generator=torch.Generator(device=dev).manual_seed(1), device=dev).half()
+    check(pw.gemm(X), X.double(), pw.dequant().double())
     want = pw.gemm(X)
-    buf = torch.full((m * n + 16,), 7.0, dtype=torch.float16, device=dev)
-    pw.gemm(X, buf[1:1 + m * n].view(m, n))
-    assert torch.equal(buf[1:1 + m * n].view(m, n), want)
-    assert (buf[:1] == 7).all() and (buf[1 + m * n:] == 7).all()
+    for at in (1, 2, 3):
+        buf = torch.full((m * n + 16,), 7.0, dtype=torch.float16, device=dev)
+        pw.gemm(X, buf[at:at + m * n].view(m, n))
+        assert torch.equal(buf[at:at + m * n].view(m, n), want)
+        assert (buf[:at] == 7).all() and (buf[at + m * n:] == 7).all()
 
 
 def test_tile_one_hot_rows(gpu):
