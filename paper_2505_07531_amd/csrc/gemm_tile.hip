@@ -141,7 +141,7 @@ template <int BITS, int KIND, int G, int MT, int NT, int WM, int SC, int KS, boo
           int WAVES = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>::kWaves>
 __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
     const char* __restrict__ packed, const void* __restrict__ Xv, const float* __restrict__ sx,
-    uint16_t* __restrict__ Y, int n, int k, int m, int nx, int my) {
+    uint16_t* __restrict__ Y, int n, int k, int m, int nx, int my, int groups) {
   using TS = TileShape<BITS, KIND, G, MT, NT, WM, SC, KS>;
   using TR = TileReads<BITS, KIND, G, MT, NT, WM, SC, KS, A8>;
   constexpr int NTH = TR::NTH, BM = TS::BM, BN = TS::BN, NG = TS::NG, kXB = TR::kXB, kMRow = TR::kMRow;
@@ -156,17 +156,11 @@ __global__ __launch_bounds__(THREADS, WAVES) void gemm_tile_kernel(
   char* const mts = cts + 2 * TS::kCBuf;
   uint32_t* const q4lut = reinterpret_cast<uint32_t*>(lds + KS * TS::kWaveLds);
 
-  // Block -> (weight tile bn, activation tile bm). Workgroups are dealt to the 8 XCDs
-  // round-robin; every XCD takes an equal run of the tiles, which are numbered in squares of
-  // up to 8 activation tiles by consecutive weight tiles, so that the tiles in flight in its
-  // L2 share both. (A run of whole weight tiles an XCD leaves units idle when they are few:
-  // 1024x5120 uniform-4 g32 at m = 683, 22 x 11 tiles: 46 us against 31 before.)
   const int total = nx * my, share = (total + 7) >> 3, at = blockIdx.x >> 3;
   const int tile = (int)(blockIdx.x & 7) * share + at;
   if (tile >= total) return;  // whole block, before any barrier
-  const int hi = tile / (nx * 8), gsz = min(8, my - hi * 8), rem = tile - hi * nx * 8;
-  const int bm = hi * 8 + rem % gsz, bn = rem / gsz;
-  const int n0 = bn * BN, m0 = bm * BM;
+  const TileAt block = tile_at(tile, nx, my, groups);
+  const int n0 = block.bn * BN, m0 = block.bm * BM;
   const int C = k >> 7, G_row = k / G;
   const size_t meta_off = (size_t)n * k * BITS / 8;
   const int t = KS > 1 ? threadIdx.x & 63 : threadIdx.x, lane = t & 63, g = lane >> 4, li = lane & 15;
@@ -517,7 +511,7 @@ int launch_cfg(const qx_desc* d, const void* packed, int m, const void* X, const
   const int nx = (d->n + TS::BN - 1) / TS::BN, my = (m + TS::BM - 1) / TS::BM;
   const unsigned blocks = ((unsigned)nx * (unsigned)my + 7u) / 8u * 8u;
   hipLaunchKernelGGL((gemm_tile_kernel<BITS, KIND, G, MT, NT, WM, SC, KS, A8>), dim3(blocks), dim3(TS::kThreads), 0,
-                     s, static_cast<const char*>(packed), X, sx, Y, d->n, d->k, m, nx, my);
+                     s, static_cast<const char*>(packed), X, sx, Y, d->n, d->k, m, nx, my, tile_groups(my));
   return hipGetLastError() == hipSuccess ? QX_OK : QX_E_HIP;
 }
 

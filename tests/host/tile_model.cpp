@@ -2,10 +2,15 @@
 //   reads  checks where the loads of every built kernel read: every thread, piece and chunk, for
 //          1 .. BM activation rows and 1 .. BN weight rows in a block; prints one line per kernel
 //          with the number of loads that leave their buffer by either rule of the range check
+//   order  reads "nx my" and prints 1 when every tile has one number, and the most weight tiles in
+//          the run of one of the 8 XCDs
 //   route  reads "bits kind group a8 n k m" from standard input (more than 4 rows) and prints the
 //          kernel that qx_gemm or qx_gemm_a8 launches: the letter of a tiled shape, or its file
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
+#include <set>
+#include <vector>
 
 #include "../../paper_2505_07531_amd/csrc/gemm_skinny_plan.h"
 #include "../../paper_2505_07531_amd/csrc/gemm_tile_plan.h"
@@ -106,6 +111,26 @@ int main(int argc, char** argv) {
   if (argc == 2 && std::strcmp(argv[1], "reads") == 0) {
 #define CHECK(B, K, G) check_format<B, K, G, false>(), check_format<B, K, G, true>();
     QX_TILE_FORMATS(CHECK)
+    return 0;
+  }
+  if (argc == 2 && std::strcmp(argv[1], "order") == 0) {
+    int nx, my;
+    while (std::scanf("%d %d", &nx, &my) == 2) {
+      std::vector<int> seen(nx * my);
+      bool once = true;
+      size_t most = 0;
+      const int share = (nx * my + 7) / 8;
+      for (int x = 0; x < 8; ++x) {
+        std::set<int> weights;
+        for (int t = x * share; t < std::min((x + 1) * share, nx * my); ++t) {
+          const TileAt at = tile_at(t, nx, my, tile_groups(my));
+          once &= at.bn >= 0 && at.bn < nx && at.bm >= 0 && at.bm < my && seen[at.bn * my + at.bm]++ == 0;
+          weights.insert(at.bn);
+        }
+        most = std::max(most, weights.size());
+      }
+      std::printf("%d %zu\n", (int)once, most);
+    }
     return 0;
   }
   if (argc == 2 && std::strcmp(argv[1], "route") == 0) {

@@ -36,6 +36,16 @@ def test_tile_loads_stay_in_their_buffers(tile_model):
     assert not bad, (len(bad), bad[:8])
 
 
+def test_tile_order(tile_model):
+    """Every tile is numbered once, and no XCD's run of tiles takes in many more weight tiles
+    than an equal share of them needs (nx / 8 of them times the groups of activation tiles)."""
+    cases = [(nx, my) for nx in (1, 2, 7, 8, 31, 64, 86) for my in (1, 2, 7, 8, 9, 10, 15, 16, 17, 25, 33, 57, 65)]
+    for (nx, my), line in zip(cases, tile_model("order", "".join(f"{nx} {my}\n" for nx, my in cases))):
+        once, most = (int(v) for v in line.split())
+        assert once, (nx, my)
+        assert most <= nx * ((my + 7) // 8) // 8 * 1.3 + 2, (nx, my, most)
+
+
 FORMATS = {f"{'uc'[kind]}{b}g{g}": (b, kind, g) for b in (3, 4) for kind in (0, 1) for g in (32, 64, 128)}
 FORMATS["q4x"] = (4, 2, 64)
 
