@@ -497,7 +497,14 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
       break;
     }
     case 2:
-      // 17 to 64 rows: several rounds of tiles, or short rows (small_tiles_win in gemm_tile_plan.h)
+      // 17 to 64 rows: several rounds of tiles, or short rows (small_tiles_win in gemm_tile_plan.h).
+      // Rows of more than 64 chunks with so few tiles: the k split over 8 waves (codebook-4 g32).
+      if constexpr (wide_small_tiles<BITS, KIND, G, A8>) {
+        if (d->k > 64 * 128 && (d->n + 31) / 32 <= 256) {
+          launch_gemm_cfg<BITS, KIND, G, 2, 1, 4, 2, 2, A8, 8>(d, p, m, X, sx, Y, s);
+          break;
+        }
+      }
       if constexpr (!(A8 && BITS == 3 && G > 32)) launch_gemm_cfg<BITS, KIND, G, 2, 1, 2, 2, kUni ? 1 : 2, A8>(d, p, m, X, sx, Y, s);
       else return QX_E_UNSUPPORTED;  // int8 rows of codebook-3 g64 and g128 always take gemm_tile.hip
       break;

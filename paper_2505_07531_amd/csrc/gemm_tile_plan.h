@@ -92,7 +92,7 @@ struct TileReads {
 // share both. (A run of whole weight tiles an XCD leaves units idle when they are few: 1024x5120
 // uniform-4 g32 at m = 683, 22 x 11 tiles: 46 us against 31.) The groups are equal: a last one of a
 // single activation tile would have one XCD read most of the codes (nine activation tiles,
-// uniform-4 g128 14336x4096 at m = 1047: 217 us as 8 + 1).
+// uniform-4 g128 14336x4096 at m = 1047: 217 us as 8 + 1, 148 as 5 + 4).
 struct TileAt {
   int bn, bm;
 };
@@ -268,6 +268,15 @@ void consider_split(const qx_desc* d, int m, float& best, int& shape) {
 //     30.3), and codebook-4 g32, whose tables leave room for one of them (11008x4096 36.9 / 43.5);
 //     rows of up to 8 chunks in 193 or 257 to 384 weight tiles (8103x768 uniform-4 6.6 / 7.2,
 //     11008x1024 codebook-4 g128 9.7 / 10.4).
+//   513 to 640 at 33 to 64 rows, where one round of 64 x 128 tiles leaves three units in eight idle:
+//     uniform-4 up to 28 chunks (18016x3072 g128 27.4 / 31.5), codebook-4 g64 32 (20432x3072 36.0 /
+//     44.0), g32 codes 24 (20432x3072 codebook-3 34.8 / 37.4).
+// Rows of 4 chunks (4 of 8 waves idle in a k split) and, above 32 rows, uniform-4 of 6 and 8, up to
+// 256 weight tiles: 3346x512 uniform-4 g64 5.1 / 5.7, 960x512 codebook-4 g128 5.2 / 5.8, 1536x1024 uniform-4
+// g128 at m = 44 6.0 / 6.6; int8 rows of codebook-4 g128 above 256: 18016x512 8.8 / 10.7.
+// Codebook-4 g32 on rows of more than 64 chunks, up to 256 weight tiles: its 32 x 32 tiles with k
+// split over 8 waves from about one tile a unit on (chunks x tiles: 3792x12288 38.9 / 43.5, 4208x10240
+// 32.5 / 37.1, 7424x12288 44.5 / 51.9; 4368x9216 29.2 / 27.5, 3328x10240 31.0 / 30.5).
 // Q4X and codebook-4 g32 rows of few chunks: Q4X 12288x640 at m = 21 7.5 / 8.1, 4096x1024 at m = 24 5.9 / 6.3;
 // codebook-4 g32 639x640 at m = 27 5.8 / 6.1.
 template <int BITS, int KIND, int G, bool A8>
@@ -277,17 +286,20 @@ bool small_tiles_win(const qx_desc* d, int m) {
   const int chunks = d->k / 128, tiles = (d->n + 31) / 32;
   if (kQ4x && tiles <= (m <= 32 ? 256 : 512) && chunks <= (A8 ? 7 : 8)) return true;
   if (kCb4g32 && !A8 && tiles <= 256 && chunks <= 8) return true;
+  if (BITS == 4 && !A8 && !kQ4x && tiles <= 256 && (chunks <= 4 || (KIND == QX_UNIFORM && m > 32 && chunks <= 8 && chunks % 2 == 0))) return true;
   if (m <= 32) {
-    if (tiles <= 256) return false;
+    if (tiles <= 256) return wide_small_tiles<BITS, KIND, G, A8> && chunks > 64 && tiles * chunks > 11000;
     const bool two = tiles <= 512;
     if (kQ4x) return chunks <= (A8 ? (two ? 16 : 40) : two ? 40 : kAll);
     if (KIND == QX_UNIFORM) return chunks <= (BITS == 3 ? (two ? 12 : 16) : !two ? kAll : tiles <= 384 ? 40 : 16);
     if (BITS == 3) return chunks <= (G == 32 ? (A8 ? (two ? 12 : 16) : two ? 16 : kAll) : A8 ? 0 : 12);
-    if (G == 128) return chunks <= (A8 ? 0 : two ? 16 : kAll);
-    return chunks <= (G == 32 || !two ? kAll : A8 ? 16 : 40);
+    if (G == 128) return chunks <= (A8 ? 4 : two ? 16 : kAll) || (!two && chunks > 64);
+    return chunks <= (G == 32 || tiles > 384 ? kAll : A8 ? 16 : 40);
   }
   if (kCb4g32) return tiles > 256 && (tiles <= 384 ? chunks <= (A8 ? 64 : kAll) : tiles <= 512 ? chunks <= 8 : !A8 && tiles <= 600);
   if (BITS == 4 && !A8 && tiles > (KIND == QX_UNIFORM ? 192 : 256) && tiles <= 384 && chunks <= 8) return true;
+  if (tiles > 512 && tiles <= 640 && chunks > 16)
+    return KIND == QX_UNIFORM ? BITS == 4 && chunks <= 28 : chunks <= (G == 32 ? 24 : G == 64 && BITS == 4 && !kQ4x ? (A8 ? 24 : 32) : 0);
   if (tiles <= 384 || tiles > (A8 || BITS == 3 ? 512 : kQ4x ? 700 : 600)) return false;
   return chunks <= (BITS == 3 ? (A8 ? 0 : 8) : A8 && !kQ4x ? 8 : 16);
 }

@@ -56,6 +56,10 @@ int launch_gemv_a8q(const qx_desc* d, const void* packed, const int8_t* xq, cons
 template <int BITS, int G>
 constexpr bool kGemmBig8 = !(BITS == 3 && G == 32);
 
+// Whether gemm.hip has 32 x 32 tiles with k split over 8 waves for up to 32 rows.
+template <int BITS, int KIND, int G, bool A8>
+constexpr bool wide_small_tiles = KIND == QX_CODEBOOK && BITS == 4 && G == 32 && !A8;
+
 // Products of more than 16 rows in larger wave tiles, or with k split over a block's waves
 // (gemm_tile.hip), where gemm_tile_applies expects less time than from the other kernels: X fp16 [m][k] with sx null, or the
 // int8 rows of qx_quantize_a8 with their scales.
