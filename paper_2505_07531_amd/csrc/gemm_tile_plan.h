@@ -109,7 +109,11 @@ inline int tile_groups(int my) { return (my + 7) / 8; }
 // Block shapes, as activation x weight rows. Cost of a round of blocks with one, two or
 // three of them on each of the 256 compute units, in us per 32 chunks of k (measured with
 // uniform and codebook-3 g128 weights on 11008x4096, 4096x11008 and 4096x4096, m = 96 to
-// 4096; the sum over rounds reproduces every measured time within 8 %).
+// 4096). A ranking more than a clock: over 1672 products of all formats that these shapes take
+// (n = 1376 to 22016, k = 1024 to 11008, m = 24 to 4096) the sums over rounds are within 8 % of
+// the measured time for 48 %, within 15 % for 80 % and within 25 % for 95 %; at worst 36 % too low
+// (codebook-3 g64 int8 11008x1024, m = 2048: rows so short that the fixed part of a round counts) and 40 % too
+// high (codebook-4 g64 4096x11008, m = 4096).
 enum Shape { kA, kB, kC, kD, kE, kF, kG, kH, kShapes };
 struct ShapeCost {
   int bm, bn, mt, nt, wm, sc;
@@ -193,13 +197,16 @@ void consider(const qx_desc* d, int m, float& best, int& shape) {
 
 // The same cost for the kernels that took these products before (gemm.hip, gemm_a8.hip),
 // fitted to their times in the sweep:
-//   fp16 activations, uniform: 128 x 256 blocks at 76 us a round from m = 384 (11008x4096
-//     uniform-4 g128 at m = 512 / 1024 / 2048: 77 / 142 / 227 us), 128 x 64 tiles that take
-//     as long as shape E below (m = 128 / 192 / 256: 40 / 52 / 54 us against 41 / 52 / 54), for
-//     3-bit g32, which has no others, 55 to 58 and 83 to 86 us for two and three of them on a
-//     unit (4096 rows, m = 600 and 1000; 5504 at m = 768) against 53 to 54 and 72 to 78 in E or C;
-//     up to 64 / 128 / 256 tiles of 128 x 64 are split over k (4096x4096 uniform-4 at m = 100 /
-//     256 / 500: 20.6 / 25.8 / 37.6 us);
+//   fp16 activations, uniform: 128 x 256 blocks, from m = 384 where they take fewer rounds than
+//     128 x 192, at 76 us a round (11008x4096 uniform-4 g128 at m = 1024 / 2048: 142 / 227 us); otherwise
+//     128 x 64 tiles, 41 / 54 / 78 us for one, two or three of them on a unit (3-bit g32 57 and 85),
+//     5 % less with 4-bit codes, up to 64 / 128 / 256 of them split over k (4096x4096 uniform-4 at m =
+//     100 / 256 / 500: 20.6 / 25.8 / 37.6 us). All activation tiles of a weight tile run on one XCD,
+//     so the weight tiles count as a multiple of 8 (10 and 13 of them: 1168x1280 uniform-3 g128, m =
+//     2162, 35 us and 21.5 in E; 1636x11008, m = 2027, 153 and 133). Short rows take 2 us more unless
+//     two tiles fill every unit (2432x640 uniform-3 g64, m = 1144: 17.8 and 14.0 in E; 16321x1024, m = 256:
+//     20.9 and 22.9). Of 4000 products of two sweeps (n = 256 to 22016, k = 512 to 14336, m = 65 to 4096)
+//     6 are more than 3 % slower than in gemm.hip (44 before the padded tiles and the 4-bit factor);
 //   table formats: 64 x 64 tiles, 20 us + 0.07 us a tile (11008x4096 codebook-3 g128 at
 //     m = 128 / 256 / 512 / 1024 / 2048: 43 / 68 / 116 / 209 / 437 us against 40 / 53 / 73 /
 //     122 / 223 here), up to 256 tiles split over k (25 us); 257 to 512 are one round of two
@@ -225,12 +232,17 @@ float other_cost(const qx_desc* d, int m, float share) {
                      (G == 32 ? (wide ? 0.8f : 1.f) * (BITS == 3 ? 1.24f : 1.48f)
                               : (wide && BITS == 3 && G == 64 ? 0.9f : 1.f) *
                                     (BITS == 3 ? (G == 64 ? 1.f : 0.91f) : G == 64 ? 1.09f : 1.03f));
+  // gemm.hip gives all activation tiles of a weight tile to one XCD: the fullest XCD counts
+  const auto tiles = [&](int bn, int bm) { return (long)((d->n + bn - 1) / bn + 7) / 8 * 8 * ((m + bm - 1) / bm); };
+  const long mb = (m + 127) / 128, big8 = ((d->n + 255) / 256 * mb + 255) / 256;
+  if (kGemmBig8<BITS, G> && m >= 384 && big8 < ((d->n + 191) / 192 * mb + 255) / 256)
+    return at(76.f * (float)((tiles(256, 128) + 255) / 256));
+  constexpr float light = BITS == 4 ? 0.95f : 1.f;  // the 4-bit codes' shorter decoding
   const long t128 = (long)((d->n + 127) / 128) * ((m + 63) / 64);
-  if (t128 <= 256) return at(t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 31.f : 38.f);
-  if (kGemmBig8<BITS, G> && m >= 384) return at(76.f * (float)(((long)((d->n + 255) / 256) * ((m + 127) / 128) + 255) / 256));
-  const long rest = t128 % 768;
-  constexpr float us[3] = {41.f, kGemmBig8<BITS, G> ? 54.f : 57.f, kGemmBig8<BITS, G> ? 74.f : 85.f};
-  return at(us[2] * (float)(t128 / 768) + (rest ? us[(rest - 1) / 256] : 0.f));
+  if (t128 <= 256) return at(light * (t128 <= 64 ? 20.7f : t128 <= 128 ? 25.5f : wide ? 33.f : 38.f) * (tiles(128, 64) > 256 ? 1.4f : 1.f));
+  const long all = tiles(128, 64), rest = all % 768;
+  constexpr float us[3] = {41.f, kGemmBig8<BITS, G> ? 54.f : 57.f, kGemmBig8<BITS, G> ? 78.f : 85.f};
+  return at(light * (us[2] * (float)(all / 768) + (rest ? us[(rest - 1) / 256] : 0.f))) + (chunks <= 10.f && (all > t128 || all < 480) ? 2.f : 0.f);
 }
 
 // Split over k: every block's time is its fixed part and its chunks.
@@ -239,7 +251,10 @@ void consider_split(const qx_desc* d, int m, float& best, int& shape) {
   if constexpr (built<BITS, KIND, G, A8>(S)) {
     const long blocks = (long)((d->n + kShape[S].bn - 1) / kShape[S].bn) * ((m + kShape[S].bm - 1) / kShape[S].bm);
     const float rounds = (float)((blocks + 255) / 256);
-    const float us = decode_factor<BITS, KIND, G, A8>() * (kShape[S].us[0] + kShape[S].us[1] * (float)(d->k / 128)) * (rounds > 1.f ? 1.08f : 1.f) *
+    // H with 4-bit uniform codes falls behind on long rows (4656x13824 g128, m = 200: 85 us by the
+    // rest of this, 98 measured, 84 in gemm.hip)
+    const float late = S == kH && KIND == QX_UNIFORM && BITS == 4 && m > 64 && d->k > 64 * 128 ? 1.12f : 1.f;
+    const float us = decode_factor<BITS, KIND, G, A8>() * (kShape[S].us[0] + kShape[S].us[1] * (float)(d->k / 128)) * (rounds > 1.f ? 1.08f : 1.f) * late *
                      (1.f - kShape[S].us[2] + kShape[S].us[2] * rounds);
     if (us < best) {
       best = us;

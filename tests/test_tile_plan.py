@@ -151,3 +151,18 @@ def test_gpu_sizes_reach_every_built_shape(tile_model):
         b, kind, g = FORMATS[f]
         got = set(routes(tile_model, [(f, a8, *s) for s in sizes((b, kind, g), a8)]))
         assert got >= shapes, (f, a8, shapes - got)
+
+
+def test_uniform_fp16_rows_against_the_tiles_that_run(tile_model):
+    """More than 64 fp16 rows of uniform weights: gemm.hip is priced by the tiles that it launches,
+    with its weight tiles padded to the 8 XCDs (us there / in the tiled shape)."""
+    there = {("u4g128", 0, 2496, 11008, 267): (55.2, 62.4), ("u4g64", 0, 3040, 5120, 489): (42.4, 46.6),
+             ("u4g128", 0, 4277, 4096, 707): (50.3, 53.8), ("u4g128", 0, 3968, 4096, 816): (50.3, 53.6),
+             ("u4g64", 0, 4128, 5120, 500): (60.5, 64.1), ("u4g128", 0, 4656, 13824, 200): (83.7, 98.2)}
+    got = dict(zip(there, routes(tile_model, there)))
+    assert all(r == "gemm" for r in got.values()), got
+    here = {("u3g128", 0, 17024, 14336, 285): (272, 230), ("u3g64", 0, 1168, 1280, 2162): (36, 22),
+            ("u3g64", 0, 4448, 8192, 1447): (280, 147), ("u4g64", 0, 4237, 3072, 778): (59, 44),
+            ("u3g64", 0, 320, 2048, 2332): (34, 17)}
+    got = dict(zip(here, routes(tile_model, here)))
+    assert all(r in "ABCDEFGH" for r in got.values()), got
