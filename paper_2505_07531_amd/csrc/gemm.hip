@@ -515,8 +515,8 @@ static int launch_gemm_t(const qx_desc* d, const void* packed, int m, const void
         // many rows: 128 x 32 per wave in 128 x 256 blocks of 8 waves, two per SIMD, where
         // those take fewer rounds of blocks than 128 x 192 blocks of 4 waves (11008x4096
         // uniform-3 g64 at m = 2048: 248.3 us, 298.7 in those; 22016x4096 at m = 1024 241.0
-        // and 297.5). Where they take as many, the shape of gemm_tile.hip with 128 x 192
-        // blocks is the faster one.
+        // and 297.5). Where they take as many, gemm_tile.hip's shapes and the tiles below are
+        // the faster ones.
         const long mb = (m + 127) / 128;
         const long big = (long)((d->n + 191) / 192) * mb, big8 = (long)((d->n + 255) / 256) * mb;
         constexpr bool kBig8 = kGemmBig8<BITS, G>;

@@ -134,19 +134,20 @@ constexpr ShapeCost kShape[kShapes] = {
     {32, 32, 2, 2, 1, 1, {3.8f, 0.19f, 0.74f}, 8},
 };
 
-// Formats whose decoding leaves the 128 x 64 wave tile enough registers: unspilled but for int8
-// rows of codebook-3, which spill 16 (g64) and 6 (g128) and are the faster shape all the same.
+// Formats whose decoding leaves the registers of the 128 x 64 wave tile unspilled. With int8 rows
+// codebook-3 spills 16 (g64: 38 products in B 14 % longer than in D, 18352x3072 at m = 1279 260 us and
+// 188) or 6 (g128: 22 of them 2 % shorter than in D, 8192x5120 at m = 2048 192 us and 215).
 template <int BITS, int KIND, int G, bool A8>
-constexpr bool kLight = KIND == QX_UNIFORM ? !A8 : KIND == QX_CODEBOOK && BITS == 3 && G >= 64;
+constexpr bool kLight = !A8 && (KIND == QX_UNIFORM || (KIND == QX_CODEBOOK && BITS == 3 && G >= 64));
 
 // Shapes that are built: F, G and H not for the integer products of gemm_a8.hip, which split k
 // themselves (11008x4096 uniform-3 g64 at m = 64: 24.1 us there, 22.9 with F; 4096x11008 24.5
-// and 24.6 with H), nor F where its tables overflow LDS; the 128 x 64 wave tiles (A, B) for the light formats and B for
-// codebook-4 g32, whose tables let one block of any shape on a compute unit.
+// and 24.6 with H), nor F where its tables overflow LDS; the 128 x 64 wave tiles (A, B) for the light formats, and B for
+// int8 rows of codebook-3 g128 and for codebook-4 g32, whose tables let one block of any shape on a compute unit.
 template <int BITS, int KIND, int G, bool A8>
 constexpr bool built(int s) {
-  if (s == kA) return kLight<BITS, KIND, G, A8> && !A8;
-  if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && BITS == 4 && G == 32);
+  if (s == kA) return kLight<BITS, KIND, G, A8>;
+  if (s == kB) return kLight<BITS, KIND, G, A8> || (KIND == QX_CODEBOOK && ((BITS == 4 && G == 32) || (BITS == 3 && G == 128)));
   // D is at no size the cheapest by the costs below with these codebooks, whose tables leave room
   // for one block of it on a compute unit, but for two of E
   if (s == kD) return !(KIND == QX_CODEBOOK && ((BITS == 3 && G == 32) || (BITS == 4 && G == 64)));

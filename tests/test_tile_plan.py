@@ -166,3 +166,10 @@ def test_uniform_fp16_rows_against_the_tiles_that_run(tile_model):
             ("u3g64", 0, 320, 2048, 2332): (34, 17)}
     got = dict(zip(here, routes(tile_model, here)))
     assert all(r in "ABCDEFGH" for r in got.values()), got
+
+
+def test_int8_rows_of_codebook_3_avoid_the_spilling_shape(tile_model):
+    """The 128 x 64 wave tile spills 16 registers for g64 (us in B / in D), 6 for g128, where it is the faster."""
+    d = {("c3g64", 1, 18352, 3072, 1279): (260, 188), ("c3g64", 1, 21632, 3072, 784): (211, 164)}
+    assert set(routes(tile_model, d)) == {"D"}
+    assert routes(tile_model, [("c3g128", 1, 8192, 5120, 2048)]) == ["B"]  # 192 us, 215 in D
