@@ -276,7 +276,7 @@ void consider_split(const qx_desc* d, int m, float& best, int& shape) {
 //     are short: 22016 rows uniform-3 g64 at 8 / 16 / 32 chunks 10.0 / 11.8, 16.1 / 16.8, 27.3 / 25.3;
 //   257 to 512: codebook-4 g32 always (11008x4096 26.4 / 31.2), codebook-4 g64 and Q4X up to 40
 //     chunks (11008x2048 13.8 / 16.2, 11008x4096 Q4X 21.4 / 22.9; 11008x8192 41.5 / 37.6 and
-//     38.6 / 38.7), others up to 16 or 12; uniform-4 up to 384 tiles, where the shapes here have
+//     38.6 / 38.7; codebook-4 g64 from 385 tiles on always, 14224x8192 47.0 / 50.0), others up to 16 or 12; uniform-4 up to 384 tiles, where the shapes here have
 //     one round of 64 x 48 for half as many rows, up to 40 (12288x5120 g128 21.6 / 23.5; beyond,
 //     14336x5120 g32 24.1 / 23.0);
 //   33 to 64 rows: where 64 x 128 tiles leave half of the units idle (14336x1024 Q4X 12.7 / 16.7,
@@ -289,7 +289,8 @@ void consider_split(const qx_desc* d, int m, float& best, int& shape) {
 //     44.0), g32 codes 24 (20432x3072 codebook-3 34.8 / 37.4).
 // Rows of 4 chunks (4 of 8 waves idle in a k split) and, above 32 rows, uniform-4 of 6 and 8, up to
 // 256 weight tiles: 3346x512 uniform-4 g64 5.1 / 5.7, 960x512 codebook-4 g128 5.2 / 5.8, 1536x1024 uniform-4
-// g128 at m = 44 6.0 / 6.6; int8 rows of codebook-4 g128 above 256: 18016x512 8.8 / 10.7.
+// g128 at m = 44 6.0 / 6.6; from 129 tiles on uniform-3 of 4 chunks too (4672x512 g128 at m = 41 5.9 /
+// 6.5); int8 rows of codebook-4 g128 above 256: 18016x512 8.8 / 10.7.
 // Codebook-4 g32 on rows of more than 64 chunks, up to 256 weight tiles: its 32 x 32 tiles with k
 // split over 8 waves from about one tile a unit on (chunks x tiles: 3792x12288 38.9 / 43.5, 4208x10240
 // 32.5 / 37.1, 7424x12288 44.5 / 51.9; 4368x9216 29.2 / 27.5, 3328x10240 31.0 / 30.5).
@@ -303,6 +304,7 @@ bool small_tiles_win(const qx_desc* d, int m) {
   if (kQ4x && tiles <= (m <= 32 ? 256 : 512) && chunks <= (A8 ? 7 : 8)) return true;
   if (kCb4g32 && !A8 && tiles <= 256 && chunks <= 8) return true;
   if (BITS == 4 && !A8 && !kQ4x && tiles <= 256 && (chunks <= 4 || (KIND == QX_UNIFORM && m > 32 && chunks <= 8 && chunks % 2 == 0))) return true;
+  if (BITS == 3 && KIND == QX_UNIFORM && m > 32 && tiles > 128 && tiles <= 256 && chunks <= 4) return true;
   if (m <= 32) {
     if (tiles <= 256) return wide_small_tiles<BITS, KIND, G, A8> && chunks > 64 && tiles * chunks > 11000;
     const bool two = tiles <= 512;
@@ -317,7 +319,7 @@ bool small_tiles_win(const qx_desc* d, int m) {
   if (tiles > 512 && tiles <= 640 && chunks > 16)
     return KIND == QX_UNIFORM ? BITS == 4 && chunks <= 28 : chunks <= (G == 32 ? 24 : G == 64 && BITS == 4 && !kQ4x ? (A8 ? 24 : 32) : 0);
   if (tiles <= 384 || tiles > (A8 || BITS == 3 ? 512 : kQ4x ? 700 : 600)) return false;
-  return chunks <= (BITS == 3 ? (A8 ? 0 : 8) : A8 && !kQ4x ? 8 : 16);
+  return chunks <= (BITS == 3 ? (A8 ? 0 : 8) : A8 && !kQ4x ? (G == 64 ? 12 : 8) : 16);
 }
 
 template <int BITS, int KIND, int G, bool A8>

@@ -68,6 +68,7 @@ SMALL_TILES = {
     ("c3g32", 0, 20432, 3072, 36): (34.7, 37.1), ("c4g64", 1, 13824, 5120, 30): (32.6, 37.5), ("c4g128", 1, 18016, 512, 24): (8.8, 10.7),
     ("u4g64", 0, 3346, 512, 50): (5.1, 5.7), ("c4g128", 0, 960, 512, 56): (5.2, 5.8), ("u4g128", 0, 1536, 1024, 44): (6.0, 6.6),
     ("u4g128", 0, 5781, 768, 39): (6.8, 7.9), ("c4g64", 0, 3305, 512, 24): (5.2, 5.8), ("c4g32", 0, 4121, 12288, 24): (40.3, 46.3),
+    ("u3g128", 0, 4672, 512, 41): (5.9, 6.5), ("c4g64", 1, 15840, 1280, 54): (20.5, 22.9),
 }
 
 
