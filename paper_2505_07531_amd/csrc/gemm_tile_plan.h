@@ -225,9 +225,15 @@ float other_cost(const qx_desc* d, int m, float share) {
   const auto at = [&](float us) { return at_chunks<BITS, KIND, G, A8>(share * us, chunks); };
   const bool wide = d->k > 64 * 128;
   const long t64 = (long)((d->n + 63) / 64) * ((m + 63) / 64);
-  if (KIND != QX_UNIFORM)
-    return at((t64 <= 128 ? 23.f : t64 <= 256 ? (wide ? 24.f : 30.f) : t64 <= 512 && !wide && !(A8 && BITS == 3 && G == 32 && chunks < 16.f) ? 44.f : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64) * (A8 ? 1.12f : 1.f) *
-           (KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f));
+  if (KIND != QX_UNIFORM) {
+    const bool one_round = t64 <= 512 && !wide && !(A8 && BITS == 3 && G == 32 && chunks < 16.f);
+    const float us = t64 <= 128   ? 23.f
+                     : t64 <= 256 ? (wide ? 24.f : 30.f)
+                     : one_round  ? 44.f
+                                  : 20.f + (wide && t64 <= 512 ? 0.05f : 0.07f) * (float)t64;
+    const float tables = KIND == QX_CODEBOOK && BITS == 4 && G == 32 ? (t64 <= 256 ? 1.1f : 1.5f) : 1.f;
+    return at(us * (A8 ? 1.12f : 1.f) * tables);
+  }
   if (A8)
     return 6.f + 0.0015f * chunks * (float)t64 *
                      (G == 32 ? (wide ? 0.8f : 1.f) * (BITS == 3 ? 1.24f : 1.48f)
@@ -303,7 +309,9 @@ bool small_tiles_win(const qx_desc* d, int m) {
   const int chunks = d->k / 128, tiles = (d->n + 31) / 32;
   if (kQ4x && tiles <= (m <= 32 ? 256 : 512) && chunks <= (A8 ? 7 : 8)) return true;
   if (kCb4g32 && !A8 && tiles <= 256 && chunks <= 8) return true;
-  if (BITS == 4 && !A8 && !kQ4x && tiles <= 256 && (chunks <= 4 || (KIND == QX_UNIFORM && m > 32 && chunks <= 8 && chunks % 2 == 0))) return true;
+  if (BITS == 4 && !A8 && !kQ4x && tiles <= 256 &&
+      (chunks <= 4 || (KIND == QX_UNIFORM && m > 32 && chunks <= 8 && chunks % 2 == 0)))
+    return true;
   if (BITS == 3 && KIND == QX_UNIFORM && m > 32 && tiles > 128 && tiles <= 256 && chunks <= 4) return true;
   if (m <= 32) {
     if (tiles <= 256) return wide_small_tiles<BITS, KIND, G, A8> && chunks > 64 && tiles * chunks > 11000;
@@ -317,7 +325,8 @@ bool small_tiles_win(const qx_desc* d, int m) {
   if (kCb4g32) return tiles > 256 && (tiles <= 384 ? chunks <= (A8 ? 64 : kAll) : tiles <= 512 ? chunks <= 8 : !A8 && tiles <= 600);
   if (BITS == 4 && !A8 && tiles > (KIND == QX_UNIFORM ? 192 : 256) && tiles <= 384 && chunks <= 8) return true;
   if (tiles > 512 && tiles <= 640 && chunks > 16)
-    return KIND == QX_UNIFORM ? BITS == 4 && chunks <= 28 : chunks <= (G == 32 ? 24 : G == 64 && BITS == 4 && !kQ4x ? (A8 ? 24 : 32) : 0);
+    return KIND == QX_UNIFORM ? BITS == 4 && chunks <= 28
+                              : chunks <= (G == 32 ? 24 : G == 64 && BITS == 4 && !kQ4x ? (A8 ? 24 : 32) : 0);
   if (tiles <= 384 || tiles > (A8 || BITS == 3 ? 512 : kQ4x ? 700 : 600)) return false;
   return chunks <= (BITS == 3 ? (A8 ? 0 : 8) : A8 && !kQ4x ? (G == 64 ? 12 : 8) : 16);
 }

@@ -174,3 +174,11 @@ def test_int8_rows_of_codebook_3_avoid_the_spilling_shape(tile_model):
     d = {("c3g64", 1, 18352, 3072, 1279): (260, 188), ("c3g64", 1, 21632, 3072, 784): (211, 164)}
     assert set(routes(tile_model, d)) == {"D"}
     assert routes(tile_model, [("c3g128", 1, 8192, 5120, 2048)]) == ["B"]  # 192 us, 215 in D
+
+
+def test_int8_rows_of_codebook_3_never_ask_for_small_tiles(tile_model):
+    """gemm.hip has no 32 x 32 tiles for int8 rows of codebook-3 g64 and g128: 17 to 64 of them
+    always find a tiled shape."""
+    cases = [(f, 1, n, 128 * c, m) for f in ("c3g64", "c3g128") for n in (1, 40, 4096, 8200, 12300, 16390, 18000, 20480, 28672, 300000)
+             for c in (1, 2, 4, 5, 8, 12, 16, 24, 32, 64, 86, 112, 1024) for m in (17, 32, 33, 48, 64)]
+    assert set(routes(tile_model, cases)) <= set("EFGH")
